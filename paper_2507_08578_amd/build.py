@@ -34,6 +34,7 @@ CFLAGS = [
 # the accumulation registers the compiler copies them out and back on every
 # K stage of the A B kernels, and the split register budget halves occupancy)
 FILE_FLAGS = {"fft_ls.hip": ["-fno-signed-zeros"],
+              "fft_pq.hip": ["-fno-signed-zeros"],
               "gemm_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 

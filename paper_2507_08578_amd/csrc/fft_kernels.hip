@@ -447,6 +447,10 @@ bool fft_choose_config(const BoxPlan& p, size_t lds_limit, FftLaunchCfg* cfg) {
   cfg->plane_lds = plane_bytes(rb);
   cfg->reg_col = fft_reg_col_supported(p.n3);
   cfg->reg_plane = fft_reg_plane_supported(p, lds_limit);
+  cfg->pq64 = fft_plane_pq_supported(p, false, lds_limit);
+  cfg->pq32 = fft_plane_pq_supported(p, true, lds_limit);
+  cfg->pq64_sq = cfg->pq64 && fft_plane_pq_wins(p.n1, false);
+  cfg->pq32_sq = cfg->pq32 && fft_plane_pq_wins(p.n1, true);
   cfg->plane_variant = 0;
   cfg->plane_variant32 = 0;
   return true;
@@ -506,13 +510,17 @@ hipError_t launch_fft_col_inv32(const BoxPlan& p, const FftLaunchCfg& cfg, int n
 
 hipError_t launch_fft_plane(const BoxPlan& p, const FftLaunchCfg& cfg, int nb, const double* vscaled,
                             cplx* T, hipStream_t s) {
-  if (cfg.reg_plane) return launch_fft_plane_reg(p, cfg.plane_variant, nb, vscaled, T, s);
+  if (cfg.reg_plane && !(cfg.plane_variant == 0 && cfg.pq64_sq))
+    return launch_fft_plane_reg(p, cfg.plane_variant, nb, vscaled, T, s);
+  if (cfg.pq64) return launch_fft_plane_pq(p, nb, vscaled, T, s);
   return plane_generic<double2>(p, cfg, nb, vscaled, T, s);
 }
 hipError_t launch_fft_plane32(const BoxPlan& p, const FftLaunchCfg& cfg, int nb, const float* vscaled,
                               float2* T, hipStream_t s) {
   if (cfg.reg_plane && cfg.plane_variant32 == 2) return launch_fft_plane_ls32(p, nb, vscaled, T, s);
-  if (cfg.reg_plane) return launch_fft_plane_reg32(p, cfg.plane_variant32, nb, vscaled, T, s);
+  if (cfg.reg_plane && !(cfg.plane_variant32 == 0 && cfg.pq32_sq))
+    return launch_fft_plane_reg32(p, cfg.plane_variant32, nb, vscaled, T, s);
+  if (cfg.pq32) return launch_fft_plane_pq32(p, nb, vscaled, T, s);
   return plane_generic<float2>(p, cfg, nb, vscaled, T, s);
 }
 
@@ -545,6 +553,7 @@ hipError_t launch_fused_col_inv(const FusedFft& f, bool fp32, const ItemDev* D, 
 }
 
 hipError_t launch_fused_plane(const FusedFft& f, bool fp32, const ItemDev* D, hipStream_t s) {
+  if (fp32 ? f.pq32 : f.pq64) return launch_fused_plane_pq(f, fp32, D, s);
   if (f.reg_plane) return launch_fused_plane_reg(f, fp32, D, s);
   dim3 grid(f.n3_max, f.nb_max, f.nitems);
   if (fp32)

@@ -70,10 +70,11 @@ int build_host_plan(const int32_t* miller, int64_t npw, int n1, int n2, int n3, 
             [&](int x, int y) { return center(x, n1) < center(y, n1); });
   P.ext_m1.erase(std::unique(P.ext_m1.begin(), P.ext_m1.end()), P.ext_m1.end());
   P.xr = (int)P.ext_m1.size();
-  P.quarter12 = 1;
+  P.quarter12 = P.holds12 = 1;
   for (int c = 0; c < P.ncols; ++c) {
     const int a1 = center(col_m1[c], n1), a2 = center(P.col_m2[c], n2);
     if (4 * a1 < -n1 || 4 * a1 >= n1 || 4 * a2 < -n2 || 4 * a2 >= n2) P.quarter12 = 0;
+    if (4 * a1 < -n1 || 4 * a1 > n1 || 4 * a2 < -n2 || 4 * a2 > n2) P.holds12 = 0;
   }
   std::vector<int> slot(n1, -1);
   for (int e = 0; e < P.xr; ++e) slot[P.ext_m1[e]] = e;

@@ -20,6 +20,7 @@ struct HostPlan {
   int ldt = 0;         // ncols rounded up to a multiple of 16
   int xr = 0;          // distinct m1
   int quarter12 = 0;   // every centred m1 in [-n1/4, n1/4) and m2 in [-n2/4, n2/4)
+  int holds12 = 0;     // every |centred m1| <= n1/4 and |centred m2| <= n2/4
   int runs = 0;        // caller order is column order and every column is gap-free along N3
   std::vector<int> col_start;   // ncols + 1: first point (column order) of each column
   std::vector<int> col_e;       // ncols: extent slot of the column's m1

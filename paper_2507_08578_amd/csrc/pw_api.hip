@@ -600,7 +600,12 @@ pw_status fused_setup(pw_batch* b) {
     // items share a group when they use the same FFT kernels (register
     // kernels are compiled per length; the generic ones take any box)
     const bool rc = h->reg_col_ok, rp = h->reg_plane_ok;
-    bybox[{rc ? h->plan.n3 : -1, rp ? h->plan.n1 : -1, rp ? h->plan.n2 : -1}].push_back((int)i);
+    // (the two-factor plane kernels take any lengths, so their small boxes
+    // share a group, whose LDS is the largest of its items')
+    const bool p64 = rp ? h->cfg.pq64_sq : h->cfg.pq64, p32 = rp ? h->cfg.pq32_sq : h->cfg.pq32;
+    const bool own = p64 && p32 ? fft_plane_pq_large(h->plan) : rp || p64 || p32;
+    bybox[{rc ? h->plan.n3 : -1, own ? h->plan.n1 : -1, own ? h->plan.n2 : -1, p64, p32}].push_back(
+        (int)i);
   }
   for (auto& kv : bybox) {
     pw_batch::Group g;
@@ -613,6 +618,9 @@ pw_status fused_setup(pw_batch* b) {
     f.nitems = (int)ids.size();
     f.reg_col = h0->reg_col_ok;
     f.reg_plane = h0->reg_plane_ok;
+    f.pq64 = f.reg_plane ? h0->cfg.pq64_sq : h0->cfg.pq64;
+    f.pq32 = f.reg_plane ? h0->cfg.pq32_sq : h0->cfg.pq32;
+    f.pq_pmax = f.pq_waves = f.pq_wbuf = f.pq_e = f.pq_n1 = 0;
     f.plane_variant = 0;
     f.plane_variant32 = 0;
     f.col_lds = 0;
@@ -628,6 +636,7 @@ pw_status fused_setup(pw_batch* b) {
       f.col_blocks = std::max(f.col_blocks, (h->plan.ncols + h->cfg.col_tile - 1) / h->cfg.col_tile);
       f.col_lds = std::max(f.col_lds, h->cfg.col_lds);
       f.plane_lds = std::max(f.plane_lds, h->cfg.plane_lds);
+      if (f.pq64 || f.pq32) fused_pq_add(&f, h->plan);
       g.nproj_max = std::max<int>(g.nproj_max, (int)h->nproj);
       g.npw_max = std::max(g.npw_max, h->npw);
       g.npw_nb_max = std::max(g.npw_nb_max, h->npw * b->items[i].nb);
@@ -980,6 +989,7 @@ pw_status pw_ctx_create(int device, void* hip_stream, pw_ctx** out) {
   if (e == hipSuccess) e = fft_reg_set_lds_limits(c->lds_limit);
   if (e == hipSuccess) e = heev_set_lds_limit(c->lds_limit);
   if (e == hipSuccess) e = fft_ls_set_lds_limit(c->lds_limit);
+  if (e == hipSuccess) e = fft_pq_set_lds_limit(c->lds_limit);
   if (e == hipSuccess) e = density_set_lds_limit(c->lds_limit);
   if (e != hipSuccess) {
     if (c->ev_join) (void)hipEventDestroy(c->ev_join);
@@ -1078,6 +1088,7 @@ pw_status pw_ham_create(pw_ctx* ctx, const pw_ham_desc* d, pw_ham** out) {
   P.ldt = hp.ldt;
   P.xr = hp.xr;
   P.quarter12 = hp.quarter12;
+  P.holds12 = hp.holds12;
   P.runs = hp.runs;
 
   pw_status st = PW_OK;

@@ -78,6 +78,7 @@ struct BoxPlan {
   int* pt_m3;               // npw: box index m3 of the k-th point (column order)
   int* ext_m1;              // xr: box index m1 of extent slot e
   int quarter12;            // 1: every point's centred m1 and m2 lie in [-N/4, N/4)
+  int holds12;              // 1: every |centred m1| <= N1/4 and |centred m2| <= N2/4
   // 1: the caller's order is the column order (pt_perm is the identity); a
   // column's points then hold consecutive centred m3 from col_m3lo[c] up
   // (the sphere is convex along N3), so the column kernels need no per-point
@@ -156,6 +157,8 @@ struct FusedFft {
   int nitems, nb_max, ncols_max, xr_max;
   bool reg_col, reg_plane;
   int plane_variant, plane_variant32;
+  bool pq64, pq32;                     // two-factor plane kernel (fft_pq.hip), items of any box
+  int pq_pmax, pq_waves, pq_wbuf, pq_e, pq_n1;   // its shape: maxima over the items
   int col_blocks;                      // generic column grid: max over items of ceil(ncols / tile)
   size_t col_lds, plane_lds;           // generic kernels, largest item
 };
@@ -169,6 +172,8 @@ struct FftLaunchCfg {
   size_t col_lds, plane_lds;
   bool reg_col;             // register-resident column kernels available for N3
   bool reg_plane;           // register-resident plane kernel available for (N1, N2)
+  bool pq64, pq32;          // the two-factor plane kernels (fft_pq.hip) hold this box
+  bool pq64_sq, pq32_sq;    // and take the place of the register kernel's variant 0
   int plane_variant;        // FP64 register plane kernel: 0 = lane groups <= 16, 1 = <= 8
   int plane_variant32;      // FP32: 0 / 1 as above, 2 = LDS-exchange kernel (fft_ls.hip)
 };
@@ -267,6 +272,17 @@ bool fft_plane_ls_supported(const BoxPlan& p, size_t lds_limit);
 hipError_t launch_fft_plane_ls32(const BoxPlan& p, int nb, const float* vscaled, float2* T,
                                  hipStream_t s);
 hipError_t fft_ls_set_lds_limit(size_t bytes);
+// Plane kernels for any pair of lengths in their list (fft_pq.hip).
+bool fft_plane_pq_supported(const BoxPlan& p, bool fp32, size_t lds_limit);
+hipError_t launch_fft_plane_pq(const BoxPlan& p, int nb, const double* vscaled, cplx* T,
+                               hipStream_t s);
+hipError_t launch_fft_plane_pq32(const BoxPlan& p, int nb, const float* vscaled, float2* T,
+                                 hipStream_t s);
+hipError_t fft_pq_set_lds_limit(size_t bytes);
+bool fft_plane_pq_large(const BoxPlan& p);   // FP64 extent array over 64 KiB
+bool fft_plane_pq_wins(int n, bool fp32);    // on n x n planes, over the lane-shuffle kernel
+void fused_pq_add(FusedFft* f, const BoxPlan& p);   // widen f's two-factor shape to hold p
+hipError_t launch_fused_plane_pq(const FusedFft& f, bool fp32, const ItemDev* D, hipStream_t s);
 
 // Electron density (density.hip; generic form in fft_kernels.hip)
 hipError_t launch_density_planes_reg(const BoxPlan& p, int nbc, const cplx* T, const double* w,
