@@ -265,6 +265,48 @@ __device__ __forceinline__ void pq_rows(C* E, int trs, int rows, pq_entry<C, SPL
   }
 }
 
+// Rows of the plane, backward along N1 only: part[row][j1] (+)= wb |.|^2.  The
+// element of a lane and task is the same for every band, so the sums in part
+// (the workgroup's own, in its L2) have one writer.
+template <class C, int N, bool SPLIT>
+__device__ __forceinline__ void pq_rows_density(const C* E, int trs, int rows,
+                                                pq_entry<C, SPLIT>* wbuf, const int* slot,
+                                                const C* __restrict__ tw, double wb, bool fresh,
+                                                double* part, const PqArgs& A) {
+  using F = Pq<C, N, SPLIT>;
+  const int lane = pq_here(A.lane), g = lane / F::P, lb = lane - g * F::P;
+  if (g >= F::GPW) return;
+  pq_entry<C, SPLIT>* buf = wbuf + g * F::BUF;
+  F f;
+  f.load(lb, pq_here(tw));
+  int sl[F::P];
+#pragma unroll
+  for (int a = 0; a < F::P; ++a)
+    if (F::live(a)) {
+      const int s = lb < F::Q ? slot[F::Q * a + lb] : -1;
+      sl[a] = s >= 0 ? s * trs : -1;
+    }
+  const int stride = (rows + F::GPW - 1) / F::GPW;
+  for (int t = A.wave; t < stride; t += A.nw) {
+    const int row = t + stride * g;
+    if (row >= rows) continue;
+    double* d = part + (size_t)row * N + lb;
+    double old[F::Q];
+#pragma unroll
+    for (int k = 0; k < F::Q; ++k) old[k] = fresh ? 0.0 : d[F::P * k];
+    C v[F::P];
+#pragma unroll
+    for (int a = 0; a < F::P; ++a)
+      if (F::live(a)) v[a] = sl[a] >= 0 ? E[sl[a] + row] : czero<C>();
+    f.bwd1(v, buf, lb);
+    f.bwd2(v, buf, lb);
+    wave_lds_fence();
+#pragma unroll
+    for (int k = 0; k < F::Q; ++k)
+      d[F::P * k] = old[k] + wb * (v[k].x * v[k].x + v[k].y * v[k].y);
+  }
+}
+
 // Columns of the sphere per thread kept in registers from one plane to the
 // next (the next plane's are loaded while the current one is transformed);
 // plans with more columns load the rest directly.
@@ -375,6 +417,8 @@ template <class C, int PMAX>
 constexpr int pq_max_waves() {
   return PMAX <= 8 ? 8 : std::min(16, 4 * pq_simd_waves<C, PMAX>());
 }
+#define PQ_BOUNDS_D \
+  __launch_bounds__((64 * pq_max_waves<double2, PMAX>()), (pq_simd_waves<double2, PMAX>()))
 #define PQ_BOUNDS __launch_bounds__((64 * pq_max_waves<C, PMAX>()), (pq_simd_waves<C, PMAX>()))
 
 template <class C, int PMAX>
@@ -382,6 +426,59 @@ __global__ void PQ_BOUNDS
 k_plane_pq(BoxPlan Pl, const C* __restrict__ tw1, const C* __restrict__ tw2,
            const real_t<C>* __restrict__ vs, C* __restrict__ T, int nplanes, int wbuf) {
   plane_pq_body<C, PMAX>(Pl, tw1, tw2, vs, T, blockIdx.x, nplanes, gridDim.x, wbuf);
+}
+
+// Electron density of one z-plane and band group: bands b = g, g + ngroup, ...
+// of the chunk, backward along N2 and N1, w_b |.|^2 added to the group's
+// partial array part[g][j3][j2][j1] (add: it already holds earlier chunks).
+// Bound like the H*psi planes; 108 x 80 x 72, 192 bands: 2.64 ms with the
+// general kernel, 0.64 here.
+template <int PMAX>
+__global__ void PQ_BOUNDS_D
+k_density_pq(BoxPlan Pl, const double2* __restrict__ tw1, const double2* __restrict__ tw2,
+             const double2* __restrict__ T, int nbc, const double* __restrict__ w, int ngroup,
+             double* __restrict__ part, int add, int wbuf) {
+  using C = double2;
+  extern __shared__ __align__(16) char lds_raw[];
+  constexpr bool SPLIT = pq_split<C, PMAX>();
+  const int n1 = Pl.n1, n2 = Pl.n2, xr = Pl.xr, ncols = Pl.ncols, trs = n2 | 1;
+  const int tid = threadIdx.x, nt = blockDim.x, j3 = blockIdx.x, g = blockIdx.y;
+  C* E = reinterpret_cast<C*>(lds_raw);
+  pq_entry<C, SPLIT>* X = reinterpret_cast<pq_entry<C, SPLIT>*>(E + (size_t)xr * trs);
+  int* slot = reinterpret_cast<int*>(X + (size_t)(nt >> 6) * wbuf);
+  PqArgs A;
+  A.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  A.nw = nt >> 6;
+  A.lane = tid & 63;
+  X += (size_t)A.wave * wbuf;
+  double* pp = part + ((size_t)g * Pl.n3 + j3) * n2 * n1;
+  if (g >= nbc && !add)   // a group without bands in the first chunk starts from zero
+    for (int i = tid; i < n2 * n1; i += nt) pp[i] = 0.0;
+  for (int i = tid; i < n1; i += nt) slot[i] = -1;
+  __syncthreads();
+  for (int e = tid; e < xr; e += nt) slot[Pl.ext_m1[e]] = e;
+  const int zlo = min(n2, n2 / 4 + 16), zhi = max(zlo, n2 - n2 / 4 - 16), zn = zlo + n2 - zhi;
+  bool fresh = !add;
+  for (int b = g; b < nbc; b += ngroup) {
+    const C* tp = T + ((size_t)b * Pl.n3 + j3) * Pl.ldt;
+    __syncthreads();   // the previous band's rows are done with E
+    for (int i = tid; i < xr * zn; i += nt) {
+      const int e = i / zn, j = i - e * zn;
+      E[e * trs + (j < zlo ? j : j - zlo + zhi)] = czero<C>();
+    }
+    __syncthreads();
+    for (int c = tid; c < ncols; c += nt) E[Pl.col_e[c] * trs + Pl.col_m2[c]] = tp[c];
+    __syncthreads();
+#define PQ_CALL(N) pq_cols<C, N, SPLIT, +1>(E, trs, xr, X, tw2, A)
+    PQ_SWITCH(n2)
+#undef PQ_CALL
+    __syncthreads();
+    const double wb = w[b];
+#define PQ_CALL(N) pq_rows_density<C, N, SPLIT>(E, trs, n2, X, slot, tw1, wb, fresh, pp, A)
+    PQ_SWITCH(n1)
+#undef PQ_CALL
+    fresh = false;
+  }
 }
 
 // fused batch: one plane per workgroup, item = blockIdx.z, lengths and tables from its descriptor
@@ -569,6 +666,31 @@ hipError_t launch_fused_plane_pq(const FusedFft& f, bool fp32, const ItemDev* D,
   return fp32 ? fused_plane_pq<float2>(f, D, s) : fused_plane_pq<double2>(f, D, s);
 }
 
+// Square planes, against the register kernel of density.hip (same sizes as
+// above): 36 97 against 221 us, 72 970 / 1060, 128 1270 / 1560; the others 24 45 /
+// 43, 48 231 / 221, 64 653 / 518, 96 976 / 923, 120 1055 / 1067, 144 1253 / 1163.
+bool density_pq_wins(int n) { return n == 36 || n == 72 || n == 128; }
+
+int density_pq_groups(const BoxPlan& p, int cus, int most) {
+  int waves, per_cu;
+  pq_shape<double2>(p, g_pq_lds_limit, &waves, &per_cu);
+  return std::max(1, std::min(most, 4 * cus * per_cu / p.n3));
+}
+
+hipError_t launch_density_planes_pq(const BoxPlan& p, int nbc, const cplx* T, const double* w,
+                                    int ngroup, double* part, int add, hipStream_t s) {
+  int waves, per_cu;
+  pq_shape<double2>(p, g_pq_lds_limit, &waves, &per_cu);
+  if (waves < 1) return hipErrorInvalidValue;
+  const size_t lds = pq_lds<double2>(p, waves);
+  const int wbuf = pq_wave_buf<double2>(p.n1, p.n2, pq_box_p(p));
+  pq_dispatch(pq_box_p(p), [&](auto pm) {
+    hipLaunchKernelGGL((k_density_pq<pm.value>), dim3(p.n3, ngroup), dim3(64 * waves), lds, s, p,
+                       p.ax1.tw, p.ax2.tw, T, nbc, w, ngroup, part, add, wbuf);
+  });
+  return hipGetLastError();
+}
+
 hipError_t fft_pq_set_lds_limit(size_t bytes) {
   g_pq_lds_limit = bytes;
   int dev = 0, cus = 0;
@@ -576,7 +698,9 @@ hipError_t fft_pq_set_lds_limit(size_t bytes) {
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
     g_pq_cus = cus;
 #define FN(C, PM) (const void*)k_plane_pq<C, PM>, (const void*)kb_plane_pq<C, PM>
-  const void* fns[16] = {FN(double2, 8), FN(float2, 8), FN(double2, 10), FN(double2, 12), FN(double2, 16),
+  const void* fns[20] = {(const void*)k_density_pq<8>, (const void*)k_density_pq<10>,
+                         (const void*)k_density_pq<12>, (const void*)k_density_pq<16>,
+                         FN(double2, 8), FN(float2, 8), FN(double2, 10), FN(double2, 12), FN(double2, 16),
                          FN(float2, 10),  FN(float2, 12),  FN(float2, 16)};
 #undef FN
   for (const void* f : fns) {

@@ -1338,13 +1338,18 @@ pw_status pw_density(pw_ham* h, int64_t nb, const void* psi, int64_t ldpsi, cons
       return fail(c, PW_ERR_INVALID_ARG, "rho and w overlap");
   }
   HIPCHK(c, hipSetDevice(c->device));
-  const bool reg = density_reg_supported(P, c->lds_limit);
+  bool reg = density_reg_supported(P, c->lds_limit);
+  const bool pq = h->cfg.pq64 && (!reg || density_pq_wins(P.n1));
+  reg = reg && !pq;
   if (!h->rho_part) {
     // about four workgroups per compute unit over the z-planes (and row
     // parts), at least one band per group and chunk
     const int64_t per = (int64_t)P.n3 * (reg ? density_row_parts(P) : 1);
     const int64_t want = (4 * (int64_t)c->cus + per - 1) / per;
-    const int groups = (int)std::max<int64_t>(1, std::min<int64_t>({want, 64, h->chunk_alloc}));
+    // (two-factor kernel: at most four whole rounds of resident workgroups)
+    const int most = (int)std::min<int64_t>(64, h->chunk_alloc);
+    const int groups = pq ? density_pq_groups(P, c->cus, most)
+                          : (int)std::max<int64_t>(1, std::min<int64_t>(want, most));
     if ((st = dalloc(h, &h->rho_part, (size_t)groups * nbox)) != PW_OK) return st;
     h->rho_groups = groups;
   }
@@ -1359,6 +1364,8 @@ pw_status pw_density(pw_ham* h, int64_t nb, const void* psi, int64_t ldpsi, cons
     StageScope sc(c, PW_STAGE_DENSITY);
     HIPCHK(c, reg ? launch_density_planes_reg(P, nc, h->T, w + c0, h->rho_groups, h->rho_part,
                                               c0 > 0, s)
+               : pq ? launch_density_planes_pq(P, nc, h->T, w + c0, h->rho_groups, h->rho_part,
+                                               c0 > 0, s)
                   : launch_density_planes_gen(P, h->cfg, nc, h->T, w + c0, h->rho_groups,
                                               h->rho_part, c0 > 0, s));
   }

@@ -290,6 +290,11 @@ hipError_t launch_density_planes_reg(const BoxPlan& p, int nbc, const cplx* T, c
 hipError_t launch_density_planes_gen(const BoxPlan& p, const FftLaunchCfg& cfg, int nbc,
                                      const cplx* T, const double* w, int ngroup, double* part,
                                      int add, hipStream_t s);
+// any box of the two-factor kernels (fft_pq.hip); groups: band groups of a launch
+hipError_t launch_density_planes_pq(const BoxPlan& p, int nbc, const cplx* T, const double* w,
+                                    int ngroup, double* part, int add, hipStream_t s);
+bool density_pq_wins(int n);   // on n x n planes, over density.hip's register kernel
+int density_pq_groups(const BoxPlan& p, int cus, int most);
 hipError_t launch_density_reduce(int64_t nbox, int ngroup, const double* part, double scale,
                                  double* rho, int accumulate, hipStream_t s);
 bool density_reg_supported(const BoxPlan& p, size_t lds_limit);

@@ -55,6 +55,25 @@ def test_unequal_and_odd_boxes(pw, ctx, box):
     assert err < 2e-6, err
 
 
+@pytest.mark.parametrize("box,nb", [((16, 18, 10), 9), ((27, 45, 8), 3), ((36, 36, 12), 40),
+                                    ((108, 80, 6), 5), ((72, 72, 4), 7), ((128, 128, 4), 3),
+                                    ((75, 120, 4), 2)],
+                         ids=lambda b: "x".join(map(str, b)) if isinstance(b, tuple) else str(b))
+def test_density_boxes(pw, ctx, box, nb):
+    """Density on the same kernels' boxes: more and fewer bands than groups,
+    accumulated twice; 1e-12 of the largest value, as for the other boxes."""
+    g, recip, v, oh = problem(box, seed=nb)
+    ham = pw.Hamiltonian(ctx, g, recip, oh.kred, box, to_dev(v), None, None, nb)
+    X = np.random.default_rng(6).standard_normal((nb, len(g), 2)) @ np.array([1.0, 1.0j])
+    w = np.random.default_rng(7).uniform(0.0, 2.0, nb)
+    rho = ham.density(to_dev(X), to_dev(w))
+    ref = oracle.density(oh, X.T, w)
+    assert np.abs(to_host(rho) - ref).max() < 1e-12 * np.abs(ref).max()
+    ham.density(to_dev(X[:1]), to_dev(w[:1]), rho=rho, accumulate=True)
+    ref = ref + oracle.density(oh, X[:1].T, w[:1])
+    assert np.abs(to_host(rho) - ref).max() < 1e-12 * np.abs(ref).max()
+
+
 @pytest.mark.parametrize("frac,shuffle", [(0.4, False), (0.25, True), (0.1, False)])
 def test_sphere_forms(pw, ctx, frac, shuffle):
     """A sphere beyond N/4 (general kernel), shuffled points, few columns."""
