@@ -770,15 +770,11 @@ __device__ __forceinline__ void splitk_reduce32_body(int64_t M, int64_t N, int n
                                                      float2* __restrict__ C, int64_t ldc,
                                                      __bf16* __restrict__ c3, int bx) {
   if (alpha_dev) alpha = alpha_dev[0];
-  const int64_t idx = (int64_t)bx * blockDim.x + threadIdx.x;
-  if (idx >= M * N) return;
+  const int zp = splitk_parts(nsplit), epb = (int)blockDim.x / zp;
+  const int64_t idx = (int64_t)bx * epb + threadIdx.x % epb;
   const int64_t j = idx / M, i = idx - j * M;
-  double re = 0.0, im = 0.0;
-  for (int z = 0; z < nsplit; ++z) {
-    const float2 w = work[(int64_t)z * M * N + idx];
-    re += w.x;
-    im += w.y;
-  }
+  double re, im;
+  if (!splitk_sum(work, M * N, idx, idx < M * N, nsplit, zp, re, im)) return;
   const double s = alpha * (rowscale ? rowscale[i] : 1.0);
   const float2 v = make_float2((float)(s * re), (float)(s * im));
   C[i + j * ldc] = v;
@@ -807,6 +803,15 @@ struct SplitPlan {
   int64_t tiles_m, tiles_n, nsplit, ksplit;
 };
 
+// Workgroups aimed at, as in gemm_kernels.hip: outside [1, kTargetBlocks), the
+// default, by the tiles (256 x 160 outputs over 37073 values, FP32: 128 us at
+// 4096, 105 at 2048, 92 at 512, 108 at 384; 192 x 117 over 16346: 46, 46, 32, 33).
+constexpr int kFewTiles = 32, kFewTilesTarget = 512;
+__host__ __device__ inline int split_target32(int target, int64_t tiles) {
+  if (target >= 1 && target < kTargetBlocks) return target;
+  return tiles <= kFewTiles ? kFewTilesTarget : kTargetBlocks;
+}
+
 template <int MODE>
 __host__ __device__ inline SplitPlan split_plan32(int64_t m, int64_t n, int64_t k, int target) {
   constexpr int Kc = 32;   // complex K per LDS stage of both P^H psi kernels
@@ -814,6 +819,7 @@ __host__ __device__ inline SplitPlan split_plan32(int64_t m, int64_t n, int64_t 
   p.tiles_m = (m + kBM - 1) / kBM;
   p.tiles_n = (n + kBN - 1) / kBN;
   const int64_t tiles = p.tiles_m * p.tiles_n;
+  target = split_target32(target, tiles);
   int64_t want = (target + tiles - 1) / tiles;
   // at least two K stages per split (short splits keep small products latency-light)
   const int64_t maxs = (k + Kc * 2 - 1) / (Kc * 2) > 1 ? (k + Kc * 2 - 1) / (Kc * 2) : 1;
@@ -874,9 +880,11 @@ kb_gemm_nn32(const ItemDev* __restrict__ D, int sel_c) {
 }  // namespace
 
 size_t gemm_cn32_work_elems(int64_t m, int64_t n, int64_t k, int bf16) {
-  const SplitPlan p = bf16 ? split_plan32<MODE_BF16>(m, n, k, kTargetBlocks)
-                           : split_plan32<MODE_F32>(m, n, k, kTargetBlocks);
-  return (size_t)(p.nsplit * m * n);
+  // the largest target a caller can set, and the default rule's
+  const SplitPlan p = bf16 ? split_plan32<MODE_BF16>(m, n, k, kTargetBlocks - 1)
+                           : split_plan32<MODE_F32>(m, n, k, kTargetBlocks - 1);
+  const SplitPlan q = bf16 ? split_plan32<MODE_BF16>(m, n, k, 0) : split_plan32<MODE_F32>(m, n, k, 0);
+  return (size_t)(std::max(p.nsplit, q.nsplit) * m * n);
 }
 
 hipError_t launch_gemm_cn32(int bf16, int64_t m, int64_t n, int64_t k, double alpha, const float2* A,
@@ -884,7 +892,6 @@ hipError_t launch_gemm_cn32(int bf16, int64_t m, int64_t n, int64_t k, double al
                             const double* rowscale, float2* work, hipStream_t s,
                             const double* alpha_dev, int target) {
   if (m <= 0 || n <= 0) return hipSuccess;
-  if (target < 1 || target > kTargetBlocks) target = kTargetBlocks;
   const SplitPlan p = bf16 ? split_plan32<MODE_BF16>(m, n, k, target)
                            : split_plan32<MODE_F32>(m, n, k, target);
   const dim3 grid((unsigned)(kXcds * p.tiles_m * p.tiles_n * ((p.nsplit + kXcds - 1) / kXcds)));
@@ -897,7 +904,7 @@ hipError_t launch_gemm_cn32(int bf16, int64_t m, int64_t n, int64_t k, double al
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t tot = m * n;
-  hipLaunchKernelGGL(k_splitk_reduce32, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, m, n,
+  hipLaunchKernelGGL(k_splitk_reduce32, dim3(splitk_blocks(tot, splitk_parts((int)p.nsplit))), dim3(256), 0, s, m, n,
                      (int)p.nsplit, (const float2*)work, alpha, alpha_dev, rowscale, C, ldc,
                      (__bf16*)nullptr);
   return hipGetLastError();
@@ -908,7 +915,6 @@ hipError_t launch_gemm_cn32_s3(int64_t m, int64_t n, int64_t k, double alpha, co
                                const double* rowscale, float2* work, hipStream_t s,
                                const double* alpha_dev, int target, uint16_t* c3) {
   if (m <= 0 || n <= 0) return hipSuccess;
-  if (target < 1 || target > kTargetBlocks) target = kTargetBlocks;
   const SplitPlan p = split_plan32<MODE_F32>(m, n, k, target);
   const dim3 grid((unsigned)(kXcds * p.tiles_m * p.tiles_n * ((p.nsplit + kXcds - 1) / kXcds)));
   hipLaunchKernelGGL(k_gemm_cn32_s3, grid, dim3(kThreads), 0, s, m, n, k, p.ksplit,
@@ -917,7 +923,7 @@ hipError_t launch_gemm_cn32_s3(int64_t m, int64_t n, int64_t k, double alpha, co
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t tot = m * n;
-  hipLaunchKernelGGL(k_splitk_reduce32, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, m, n,
+  hipLaunchKernelGGL(k_splitk_reduce32, dim3(splitk_blocks(tot, splitk_parts((int)p.nsplit))), dim3(256), 0, s, m, n,
                      (int)p.nsplit, (const float2*)work, alpha, alpha_dev, rowscale, C, ldc,
                      reinterpret_cast<__bf16*>(c3));
   return hipGetLastError();
@@ -928,7 +934,6 @@ hipError_t launch_gemm_cn32_s16(int64_t m, int64_t n, int64_t k, double alpha, c
                                 const double* rowscale, float2* work, hipStream_t s,
                                 const double* alpha_dev, int target) {
   if (m <= 0 || n <= 0) return hipSuccess;
-  if (target < 1 || target > kTargetBlocks) target = kTargetBlocks;
   const SplitPlan p = split_plan32<MODE_BF16>(m, n, k, target);
   const dim3 grid((unsigned)(kXcds * p.tiles_m * p.tiles_n * ((p.nsplit + kXcds - 1) / kXcds)));
   hipLaunchKernelGGL((k_gemm_cn32<MODE_BF16, bf16c>), grid, dim3(kThreads), 0, s, m, n, k,
@@ -937,7 +942,7 @@ hipError_t launch_gemm_cn32_s16(int64_t m, int64_t n, int64_t k, double alpha, c
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t tot = m * n;
-  hipLaunchKernelGGL(k_splitk_reduce32, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, m, n,
+  hipLaunchKernelGGL(k_splitk_reduce32, dim3(splitk_blocks(tot, splitk_parts((int)p.nsplit))), dim3(256), 0, s, m, n,
                      (int)p.nsplit, (const float2*)work, alpha, alpha_dev, rowscale, C, ldc,
                      (__bf16*)nullptr);
   return hipGetLastError();
@@ -1015,7 +1020,7 @@ hipError_t launch_fused_gemm_cn32(int bf16, int nitems, int64_t m_max, int64_t n
     hipLaunchKernelGGL(kb_gemm_cn32<MODE_F32>, grid, dim3(kThreads), 0, s, D, sel_b, nsplit_max);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  dim3 rgrid((m_max * n_max + 255) / 256, nitems);
+  dim3 rgrid(splitk_blocks(m_max * n_max, splitk_parts(nsplit_max)), nitems);
   if (bf16)
     hipLaunchKernelGGL(kb_splitk_reduce32<MODE_BF16>, rgrid, dim3(256), 0, s, D, alpha, coef_step);
   else

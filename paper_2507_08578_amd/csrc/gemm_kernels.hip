@@ -317,15 +317,11 @@ __device__ __forceinline__ void splitk_reduce_body(int64_t M, int64_t N, int nsp
                                                    int bx, cplx* __restrict__ Craw = nullptr,
                                                    int64_t ldraw = 0) {
   if (alpha_dev) alpha = alpha_dev[0];
-  const int64_t idx = (int64_t)bx * blockDim.x + threadIdx.x;
-  if (idx >= M * N) return;
+  const int zp = splitk_parts64(nsplit, N), epb = (int)blockDim.x / zp;
+  const int64_t idx = (int64_t)bx * epb + threadIdx.x % epb;
   const int64_t j = idx / M, i = idx - j * M;
-  double re = 0.0, im = 0.0;
-  for (int z = 0; z < nsplit; ++z) {
-    const cplx w = work[(int64_t)z * M * N + idx];
-    re += w.x;
-    im += w.y;
-  }
+  double re, im;
+  if (!splitk_sum(work, M * N, idx, idx < M * N, nsplit, zp, re, im)) return;
   if (Craw) Craw[i + j * ldraw] = make_double2(alpha * re, alpha * im);
   const double s = alpha * (rowscale ? rowscale[i] : 1.0);
   cplx v = make_double2(s * re, s * im);
@@ -385,19 +381,16 @@ k_gemm_cn_upper(int64_t M, int64_t K, int64_t ksplit, int nact, int nsplit,
 // elements of the active tiles; the rest of C is not written.
 __global__ void k_splitk_reduce_upper(int64_t M, int nsplit, int nact, const cplx* __restrict__ work,
                                       double alpha, cplx* __restrict__ C, int64_t ldc) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= M * M) return;
+  const int zp = splitk_parts64(nsplit, M), epb = (int)blockDim.x / zp;
+  const int64_t idx = (int64_t)blockIdx.x * epb + threadIdx.x % epb;
   const int64_t j = idx / M, i = idx - j * M;
   const int by = (int)(i / kBM), bx = (int)(j / kBN);
-  if (by > bx) return;
   const int64_t t = (int64_t)bx * (bx + 1) / 2 + by;
   const int64_t loc = (i - (int64_t)by * kBM) + (j - (int64_t)bx * kBN) * kBM;
-  double re = 0.0, im = 0.0;
-  for (int z = 0; z < nsplit; ++z) {
-    const cplx w = work[((int64_t)z * nact + t) * kBM * kBN + loc];
-    re += w.x;
-    im += w.y;
-  }
+  double re, im;
+  if (!splitk_sum(work, (int64_t)nact * kBM * kBN, t * kBM * kBN + loc, idx < M * M && by <= bx,
+                  nsplit, zp, re, im))
+    return;
   C[i + j * ldc] = make_double2(alpha * re, alpha * im);
 }
 
@@ -405,12 +398,19 @@ struct SplitPlan {
   int64_t tiles_m, tiles_n, nsplit, ksplit;
 };
 
-// The handle's split-K target as the FP64 products use it: values outside
-// [1, kTargetBlocks] (the FP32 products accept more) mean kTargetBlocks, as in
-// launch_gemm_cn, so fused and per-item launches split alike and stay within
-// the workspace sized for kTargetBlocks.
-__host__ __device__ inline int fp64_target(int target) {
-  return (target < 1 || target > kTargetBlocks) ? kTargetBlocks : target;
+// Workgroups a split product aims at: the caller's target, or by the output's
+// tiles where that is outside [1, kTargetBlocks] (the default; the FP32
+// products accept more).  Up to 32 tiles the partials, written and read once
+// per split, cost more than filling the chip beyond two workgroups per CU
+// gains: 256 x 160 outputs over 37073 values 259 us at 2048 workgroups, 237 -
+// 249 at 768 - 512, 303 at 384 (one and a half per CU); 192 x 117 over 16346
+// 85, 68 - 69, 79.  With more tiles few splits do anyway (864 x 512 over
+// 124289: 6.6 ms at 2048, 10.5 at 1024).  Fused and per-item launches share
+// the rule, and never exceed the workspace sized for kTargetBlocks.
+constexpr int kFewTiles = 32, kFewTilesTarget = 512;
+__host__ __device__ inline int split_target(int target, int64_t tiles) {
+  if (target >= 1 && target <= kTargetBlocks) return target;
+  return tiles <= kFewTiles ? kFewTilesTarget : kTargetBlocks;
 }
 
 __host__ __device__ inline SplitPlan split_plan(int64_t m, int64_t n, int64_t k, int target) {
@@ -418,6 +418,7 @@ __host__ __device__ inline SplitPlan split_plan(int64_t m, int64_t n, int64_t k,
   p.tiles_m = (m + kBM - 1) / kBM;
   p.tiles_n = (n + kBN - 1) / kBN;
   const int64_t tiles = p.tiles_m * p.tiles_n;
+  target = split_target(target, tiles);
   int64_t want = (target + tiles - 1) / tiles;
   // at least two K stages per split (short splits keep small products latency-light)
   const int64_t maxs = (k + kKcCN * 2 - 1) / (kKcCN * 2) > 1 ? (k + kKcCN * 2 - 1) / (kKcCN * 2) : 1;
@@ -458,7 +459,7 @@ __device__ __forceinline__ CnArgs fused_cn_args(const ItemDev& d, int op, int se
     a.C = d.cprj;
     a.ldc = d.nproj;
     a.rowscale = d.ekb;
-    a.target = fp64_target(d.gemm_target);
+    a.target = d.gemm_target;
   } else {
     a.M = d.nb;
     a.N = d.nb;
@@ -466,7 +467,7 @@ __device__ __forceinline__ CnArgs fused_cn_args(const ItemDev& d, int op, int se
     a.C = d.sub0;
     a.ldc = d.nb;
     a.rowscale = nullptr;
-    a.target = kTargetBlocks;
+    a.target = 0;
   }
   return a;
 }
@@ -528,6 +529,10 @@ size_t gemm_cn_work_elems(int64_t m, int64_t n, int64_t k) {
   return p.nsplit > 1 ? (size_t)(p.nsplit * m * n) : 0;
 }
 
+int gemm_cn_fixed_target(int target) {
+  return target >= 1 && target <= kTargetBlocks ? target : kTargetBlocks;
+}
+
 hipError_t launch_gemm_cn(int64_t m, int64_t n, int64_t k, double alpha, const cplx* A, int64_t lda,
                           const cplx* B, int64_t ldb, cplx* C, int64_t ldc, const double* rowscale,
                           cplx* work, hipStream_t s, double beta, const double* alpha_dev,
@@ -536,12 +541,12 @@ hipError_t launch_gemm_cn(int64_t m, int64_t n, int64_t k, double alpha, const c
   if (upper && (m != n || kBM != kBN || rowscale || alpha_dev || beta != 0.0))
     return hipErrorInvalidValue;
   if (craw && (upper || beta != 0.0 || ldraw < m)) return hipErrorInvalidValue;
-  if (target < 1 || target > kTargetBlocks) target = kTargetBlocks;
   SplitPlan p = split_plan(m, n, k, target);
+  target = split_target(target, p.tiles_m * p.tiles_n);
   const int64_t T = (m + kBM - 1) / kBM, nact = T * (T + 1) / 2;
   if (T == 1) upper = 0;   // a single tile: nothing to skip
-  // packed splits that fit the workspace the full product would use (p.nsplit m n)
-  const int64_t cap = p.nsplit * m * n / (nact * kBM * kBN);
+  // packed splits that fit the workspace (sized for the full product at kTargetBlocks)
+  const int64_t cap = split_plan(m, n, k, kTargetBlocks).nsplit * m * n / (nact * kBM * kBN);
   if (upper && work && p.nsplit > 1 && cap >= 1) {
     // as many splits as fill ~target blocks with the active tiles
     const int64_t maxs = (k + kKcCN * 2 - 1) / (kKcCN * 2) > 1 ? (k + kKcCN * 2 - 1) / (kKcCN * 2) : 1;
@@ -557,7 +562,8 @@ hipError_t launch_gemm_cn(int64_t m, int64_t n, int64_t k, double alpha, const c
                        dim3(kThreads), 0, s, m, k, ks, (int)nact, (int)ns, A, lda, B, ldb, work);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_splitk_reduce_upper, dim3((unsigned)((m * m + 255) / 256)), dim3(256), 0, s,
+    const int zp = splitk_parts64((int)ns, m);
+    hipLaunchKernelGGL(k_splitk_reduce_upper, dim3(splitk_blocks(m * m, zp)), dim3(splitk_threads(zp)), 0, s,
                        m, (int)ns, (int)nact, (const cplx*)work, alpha, C, ldc);
     return hipGetLastError();
   }
@@ -584,7 +590,8 @@ hipError_t launch_gemm_cn(int64_t m, int64_t n, int64_t k, double alpha, const c
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t tot = m * n;
-  hipLaunchKernelGGL(k_splitk_reduce, dim3((tot + 255) / 256), dim3(256), 0, s, m, n,
+  const int zp = splitk_parts64((int)p.nsplit, n);
+  hipLaunchKernelGGL(k_splitk_reduce, dim3(splitk_blocks(tot, zp)), dim3(splitk_threads(zp)), 0, s, m, n,
                      (int)p.nsplit, (const cplx*)work, alpha, alpha_dev, rowscale, beta, C, ldc, craw,
                      ldraw);
   return hipGetLastError();
@@ -610,8 +617,7 @@ hipError_t launch_gemm_nn(int64_t m, int64_t n, int64_t k, double alpha, const c
 }
 
 int fused_cn_nsplit(int op, int64_t npw, int64_t nb, int64_t nproj, int target) {
-  const SplitPlan p = op == GOP_PROJ ? split_plan(nproj, nb, npw, fp64_target(target))
-                                     : split_plan(nb, nb, npw, kTargetBlocks);
+  const SplitPlan p = op == GOP_PROJ ? split_plan(nproj, nb, npw, target) : split_plan(nb, nb, npw, 0);
   return (int)p.nsplit;
 }
 
@@ -624,7 +630,8 @@ hipError_t launch_fused_gemm_cn(int nitems, int64_t m_max, int64_t n_max, int ns
                      nsplit_max);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || nsplit_max == 1) return e;
-  dim3 rgrid((m_max * n_max + 255) / 256, nitems);
+  // an item of fewer splits needs fewer workgroups than the largest one
+  dim3 rgrid(splitk_blocks(m_max * n_max, splitk_parts(nsplit_max)), nitems);
   hipLaunchKernelGGL(kb_splitk_reduce, rgrid, dim3(256), 0, s, D, op, sel_b, alpha, coef_step);
   return hipGetLastError();
 }

@@ -157,9 +157,14 @@ pw_status check_hot(pw_ham* h, pw_prec prec, int64_t nb) {
 // prev is read whenever it is non-null.
 pw_status ham_apply(pw_ham* h, int64_t nb, const cplx* in, int64_t ldin, cplx* out, int64_t ldout,
                     double alpha, double beta, double gamma, const cplx* prev, int64_t ldprev,
-                    const double* coef, cplx* craw) {
+                    const double* coef, cplx* craw, bool repro) {
   pw_ctx* c = h->ctx;
   hipStream_t s = c->stream;
+  // repro (kReproBands): the split count and the FFT kernels that do not follow
+  // the shape rules
+  FftLaunchCfg cfg = h->cfg;
+  if (repro) cfg.pq64 = cfg.pq64_sq = false;
+  const int target = repro ? gemm_cn_fixed_target(h->gemm_target) : h->gemm_target;
   const bool fork = h->nproj > 0 && c->overlap && c->stream == c->home;
   if (h->nproj > 0) {
     // P^H psi on the second stream, concurrent with the FFT route below
@@ -170,7 +175,7 @@ pw_status ham_apply(pw_ham* h, int64_t nb, const cplx* in, int64_t ldin, cplx* o
     }
     StageScope sc(c, PW_STAGE_PROJ, ps);
     HIPCHK(c, launch_gemm_cn(h->nproj, nb, h->npw, alpha, h->proj, h->npw, in, ldin, h->cprj,
-                             h->nproj, h->ekb_dev, h->gemm_work, ps, 0.0, coef, h->gemm_target, 0,
+                             h->nproj, h->ekb_dev, h->gemm_work, ps, 0.0, coef, target, 0,
                              craw, h->nproj));
   }
   if (fork) HIPCHK(c, hipEventRecord(c->ev_join, c->aux));
@@ -179,15 +184,15 @@ pw_status ham_apply(pw_ham* h, int64_t nb, const cplx* in, int64_t ldin, cplx* o
     const int nc = (int)std::min<int64_t>(h->chunk, nb - c0);
     {
       StageScope sc(c, PW_STAGE_FFT_COL_INV);
-      HIPCHK(c, launch_fft_col_inv(h->plan, h->cfg, nc, in + c0 * ldin, ldin, h->T, s));
+      HIPCHK(c, launch_fft_col_inv(h->plan, cfg, nc, in + c0 * ldin, ldin, h->T, s));
     }
     {
       StageScope sc(c, PW_STAGE_FFT_PLANE);
-      HIPCHK(c, launch_fft_plane(h->plan, h->cfg, nc, h->vscaled, h->T, s));
+      HIPCHK(c, launch_fft_plane(h->plan, cfg, nc, h->vscaled, h->T, s));
     }
     {
       StageScope sc(c, PW_STAGE_FFT_COL_FWD);
-      HIPCHK(c, launch_fft_col_fwd(h->plan, h->cfg, nc, h->T, h->kin, in + c0 * ldin, ldin,
+      HIPCHK(c, launch_fft_col_fwd(h->plan, cfg, nc, h->T, h->kin, in + c0 * ldin, ldin,
                                    prev ? prev + c0 * ldprev : nullptr, ldprev, out + c0 * ldout,
                                    ldout, ep, s));
     }
@@ -395,6 +400,9 @@ pw_status chol_and_solve(pw_ham* h, int64_t nb, cplx* y, int64_t ld, cplx* hy, i
   return PW_OK;
 }
 
+// split target of the Gram matrices (kReproBands)
+int gram_target(int64_t nb) { return nb > kReproBands ? gemm_cn_fixed_target(0) : 0; }
+
 // Cholesky orthonormalisation of a block: Gram in FP64, blocked Cholesky,
 // Y <- Y U^{-1} (and HY alike); a failing pivot goes to the context's
 // deferred status under op.  gram_prec FP32 / BF16: a first pass whose Gram
@@ -425,7 +433,7 @@ pw_status ortho_block(pw_ham* h, int64_t nb, cplx* y, int64_t ld, cplx* hy, int6
     StageScope sc(c, PW_STAGE_GRAM);
     // Hermitian: the tiles on and above the diagonal, then mirrored
     HIPCHK(c, launch_gemm_cn(nb, nb, h->npw, 1.0, y, ld, y, ld, h->sub0, nb, nullptr, h->gemm_work, s,
-                             0.0, nullptr, 2048, 1));
+                             0.0, nullptr, gram_target(nb), 1));
     HIPCHK(c, launch_hermitize(nb, h->sub0, nb, s));
   }
   return chol_and_solve(h, nb, y, ld, hy, ldhy, op, cp);
@@ -441,7 +449,7 @@ pw_status subspace_rr(pw_ham* h, int64_t nb, cplx* y, int64_t ld, cplx* hy, int6
   {
     StageScope sc(c, PW_STAGE_GRAM);
     HIPCHK(c, launch_gemm_cn(nb, nb, h->npw, 1.0, y, ld, hy, ldhy, h->sub0, nb, nullptr,
-                             h->gemm_work, s, 0.0, nullptr, 2048, 1));
+                             h->gemm_work, s, 0.0, nullptr, gram_target(nb), 1));
     HIPCHK(c, launch_hermitize(nb, h->sub0, nb, s));
   }
   {
@@ -528,14 +536,14 @@ pw_status batch_ortho_rr(BatchItem& it) {
   hipStream_t s = c->stream;
   const int64_t nb = it.nb, npw = h->npw;
   HIPCHK(c, launch_gemm_cn(nb, nb, npw, 1.0, it.y, npw, it.y, npw, h->sub0, nb, nullptr,
-                           h->gemm_work, s, 0.0, nullptr, 2048, 1));
+                           h->gemm_work, s, 0.0, nullptr, 0, 1));
   HIPCHK(c, launch_hermitize(nb, h->sub0, nb, s));
   HIPCHK(c, chol_blocked(nb, h->sub0, nb, h->dinv, h->panel, h->dtol, h->status_dev, s));
   HIPCHK(c, trsm_right(npw, nb, it.y, npw, h->sub0, nb, h->dinv, h->blk, s));
   pw_status st = ham_apply(h, nb, it.y, npw, it.hy, npw, 1.0, 0.0, 0.0, nullptr, 0);
   if (st != PW_OK) return st;
   HIPCHK(c, launch_gemm_cn(nb, nb, npw, 1.0, it.y, npw, it.hy, npw, h->sub0, nb, nullptr,
-                           h->gemm_work, s, 0.0, nullptr, 2048, 1));
+                           h->gemm_work, s, 0.0, nullptr, 0, 1));
   HIPCHK(c, launch_hermitize(nb, h->sub0, nb, s));
   HIPCHK(c, launch_heev_small_async(nb, h->sub0, nb, it.eig, h->sub1, nb, it.sweeps, s));
   if ((st = rotate_block(h, nb, it.y, npw, h->sub1)) != PW_OK) return st;
@@ -1508,7 +1516,8 @@ pw_status pw_rayleigh_ritz(pw_ham* h, int64_t nb, void* yv, int64_t ld, void* hy
   cplx* y = static_cast<cplx*>(yv);
   cplx* hy = static_cast<cplx*>(hyv);
   h->cprj_nb = 0;
-  if ((st = ham_apply(h, nb, y, ld, hy, ldhy, 1.0, 0.0, 0.0, nullptr, 0, nullptr, h->cprj_y)) != PW_OK)
+  if ((st = ham_apply(h, nb, y, ld, hy, ldhy, 1.0, 0.0, 0.0, nullptr, 0, nullptr, h->cprj_y,
+                      nb > kReproBands)) != PW_OK)
     return st;
   if ((st = subspace_rr(h, nb, y, ld, hy, ldhy, eig, resid, kOpRayleighRitz, h->cprj_y)) != PW_OK)
     return st;

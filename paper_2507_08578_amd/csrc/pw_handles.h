@@ -98,7 +98,7 @@ struct pw_ham {
   int64_t chunk = 0;         // bands per FFT launch (tunable, <= chunk_alloc)
   int64_t chunk_alloc = 0;   // bands the FFT work buffer holds
   int gemm_target = 4096;    // split-K target block count of the projector product (tunable;
-                             // the FP64 product caps it at 2048)
+                             // 4096, and for FP64 above 2048: by the shape)
   int nn_tile = 0;           // workgroup tile of the tall FP64 products P C, Y Q, Y U^-1 (tunable)
   int nn_tile32 = 0;         // the same for the FP32 / BF16 product P C (tunable)
   bool reg_col_ok = false, reg_plane_ok = false, narrow_ok = false, narrow32_ok = false;
@@ -219,7 +219,7 @@ pw_status check_hot(pw_ham* h, pw_prec prec, int64_t nb);
 // projections before the KB energies scale them.
 pw_status ham_apply(pw_ham* h, int64_t nb, const cplx* in, int64_t ldin, cplx* out, int64_t ldout,
                     double alpha, double beta, double gamma, const cplx* prev, int64_t ldprev,
-                    const double* coef = nullptr, cplx* craw = nullptr);
+                    const double* coef = nullptr, cplx* craw = nullptr, bool repro = false);
 pw_status rotate_block(pw_ham* h, int64_t nb, cplx* y, int64_t ld, const cplx* m);
 // Hot calls that record a deferred status (pw_ctx_check names them).
 enum DeferredOp { kOpOrtho = 1, kOpRayleighRitz = 2, kOpLobpcg = 3, kOpRmmDiis = 4, kOpHeev = 5 };

@@ -329,11 +329,12 @@ hipError_t launch_fft_col_fwd_reg16(const BoxPlan& p, int nb, const float2* T, c
 // holds splits*m*n cplx (gemm_cn_work_elems); with work == null the product
 // is not split.  rowscale (m doubles on device) may be null.
 size_t gemm_cn_work_elems(int64_t m, int64_t n, int64_t k);
+int gemm_cn_fixed_target(int target);   // target without the rule by the shape
 // alpha_dev (may be null): device scalar read in place of alpha.
 hipError_t launch_gemm_cn(int64_t m, int64_t n, int64_t k, double alpha, const cplx* A, int64_t lda,
                           const cplx* B, int64_t ldb, cplx* C, int64_t ldc, const double* rowscale,
                           cplx* work, hipStream_t s, double beta = 0.0,
-                          const double* alpha_dev = nullptr, int target_blocks = 2048,
+                          const double* alpha_dev = nullptr, int target_blocks = 0,
                           int upper = 0,    // 1 (m == n, Hermitian result): only the 64 x 64
                                             // tiles on and above the diagonal are formed
                           cplx* craw = nullptr, int64_t ldraw = 0);  // also alpha A^H B without
@@ -343,13 +344,84 @@ hipError_t launch_gemm_nn(int64_t m, int64_t n, int64_t k, double alpha, const c
                           const cplx* B, int64_t ldb, double beta, cplx* C, int64_t ldc,
                           hipStream_t s, int tile = 0);
 
+// Rayleigh-Ritz with more than kReproBands bands, and the orthonormalisation
+// before it, keep one fixed order of every sum and one choice of FP64 kernels:
+// the block Jacobi solver returns Ritz vectors whose phases move by 1e7 .. 1e8
+// times a change of the matrix (160 bands: 4e-9 for 1e-16; 64 bands: 1e-12),
+// so any other rounding there would give vectors that differ, by a phase, in
+// the eighth digit from those of a saved run.
+constexpr int64_t kReproBands = 64;
+
+// Split-K reductions: a workgroup of splitk_threads(zp) threads takes zp threads
+// to an element (thread part q takes the splits q, q + zp, ..., in
+// order, then the parts are added in order).  zp = 1, for more than kReproBands
+// columns in FP64, adds the splits one after another, 16 loads at a time in
+// flight.  One load after another leaves a small result to latency: 8 x 16
+// elements of 38 splits took 6.7 us, 256 x 160 of 168 splits 55 us (2 TB/s).
+__host__ __device__ inline int splitk_parts(int nsplit) { return nsplit > 32 ? 16 : nsplit > 8 ? 8 : 4; }
+__host__ __device__ inline int splitk_parts64(int nsplit, int64_t n) {
+  return n > kReproBands ? 1 : splitk_parts(nsplit);
+}
+inline int splitk_threads(int zp) { return zp == 1 ? 64 : 256; }
+inline unsigned splitk_blocks(int64_t elems, int zp) {
+  return (unsigned)((elems * zp + splitk_threads(zp) - 1) / splitk_threads(zp));
+}
+// sum over z of work[z stride + idx] in FP64 by the zp threads of an element;
+// only part 0 (returns true) holds the result.  Every thread of the workgroup
+// calls it.
+template <class W>
+__device__ __forceinline__ bool splitk_sum(const W* __restrict__ work, int64_t stride, int64_t idx,
+                                           bool valid, int nsplit, int zp, double& re, double& im) {
+  re = im = 0.0;
+  if (zp == 1) {
+    if (!valid) return false;
+    constexpr int U = 16;
+    int z = 0;
+    for (; z + U <= nsplit; z += U) {
+      W w[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) w[u] = work[(int64_t)(z + u) * stride + idx];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        re += w[u].x;
+        im += w[u].y;
+      }
+    }
+    for (; z < nsplit; ++z) {
+      const W w = work[(int64_t)z * stride + idx];
+      re += w.x;
+      im += w.y;
+    }
+    return true;
+  }
+  __shared__ double2 part[256];
+  const int q = threadIdx.x / (256 / zp);
+  if (valid) {
+#pragma unroll 4
+    for (int z = q; z < nsplit; z += zp) {
+      const W w = work[(int64_t)z * stride + idx];
+      re += w.x;
+      im += w.y;
+    }
+  }
+  part[threadIdx.x] = make_double2(re, im);
+  __syncthreads();
+  if (q != 0 || !valid) return false;
+  for (int p = 1; p < zp; ++p) {
+    const double2 o = part[threadIdx.x + p * (256 / zp)];
+    re += o.x;
+    im += o.y;
+  }
+  return true;
+}
+
 // Low-precision products (gemm32_kernels.hip): complex64 operands, FP32
 // accumulation; bf16 != 0 rounds the MFMA operands to bfloat16.
 size_t gemm_cn32_work_elems(int64_t m, int64_t n, int64_t k, int bf16);
 hipError_t launch_gemm_cn32(int bf16, int64_t m, int64_t n, int64_t k, double alpha, const float2* A,
                             int64_t lda, const float2* B, int64_t ldb, float2* C, int64_t ldc,
                             const double* rowscale, float2* work, hipStream_t s,
-                            const double* alpha_dev = nullptr, int target_blocks = 2048);
+                            const double* alpha_dev = nullptr, int target_blocks = 0);
 // FP32 (bf16 = 0) with a3 and b3 given: A B from the stored three-term
 // copies a3 of A (rows m, contraction k) and b3 of B^T (rows n, contraction
 // k); A and B are then not read and tile has no effect.
@@ -370,7 +442,7 @@ hipError_t launch_gemm_cn32_s3(int64_t m, int64_t n, int64_t k, double alpha, co
 hipError_t launch_gemm_cn32_s16(int64_t m, int64_t n, int64_t k, double alpha, const float2* A,
                                 int64_t lda, const bf16c* B, int64_t ldb, float2* C, int64_t ldc,
                                 const double* rowscale, float2* work, hipStream_t s,
-                                const double* alpha_dev = nullptr, int target_blocks = 2048);
+                                const double* alpha_dev = nullptr, int target_blocks = 0);
 hipError_t launch_gemm_nn32_s16(int64_t m, int64_t n, int64_t k, double alpha, const float2* A,
                                 int64_t lda, const float2* B, int64_t ldb, double beta, bf16c* C,
                                 int64_t ldc, hipStream_t s, int tile = 0);

@@ -646,7 +646,7 @@ pw_status pw_lobpcg(pw_ham* h, int64_t nb, int32_t nblock, int32_t nline, void* 
       {
         StageScope sc(c, PW_STAGE_GRAM);
         HIPCHK(c, launch_gemm_cn(k, k, npw, 1.0, V, npw, HV, npw, w.s, k, nullptr, w.work, s, 0.0,
-                                 nullptr, 2048, 1));
+                                 nullptr, 0, 1));
         HIPCHK(c, launch_hermitize(k, w.s, k, s));
       }
       {
