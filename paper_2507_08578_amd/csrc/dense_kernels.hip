@@ -418,8 +418,205 @@ inline int jac_threads(int n) {
   return t;
 }
 
-// Whole Jacobi solve in LDS for n <= 64.
-__device__ __forceinline__ void jacobi_small_body(int n, const cplx* __restrict__ Ain, int64_t lda, double* __restrict__ w,
+// Whole Jacobi solve in LDS for n <= kJacMidMax, cyclic by the circle method on
+// n padded to even (n2 = 2 h) with a zero row and column, which never rotates.
+//
+// The matrix is kept by position, not by index: position (role, k) holds the
+// index that pair k of the current round has in that role, so thread t < h^2
+// always works on block (pair t / h, pair t % h) at fixed addresses, and
+// writes it to where its indices stand in the next round, a fixed permutation:
+//   (a,0) -> (a,0), (a,1) -> (b,0), (a,k) -> (a,k-1), (b,k) -> (b,k+1),
+//   (b,h-1) -> (a,h-1);
+// m = n2 - 1 rounds bring every index back.  A and V are double-buffered, so a
+// round has one barrier and every thread forms the two rotations it needs.
+//
+// One wavefront issues an instruction about every five cycles here, so the
+// instructions of a round are its time.  Against indices by the circle method
+// in place, two barriers and the rotations formed by h threads (jacobi_64_body),
+// random matrices: n = 16 146 -> 60 us, 24 286 -> 116, 32 400 -> 156, 45 about
+// 1200 -> 513 (n odd costs that form twice as much).
+constexpr int kJacMidMax = 46;   // two copies of A and V: 135 KiB of LDS
+struct RotS {
+  double cs, t;     // cosine; change of the diagonal (0 where no rotation)
+  cplx s;           // sn ph
+};
+// y = 1/sqrt(x): one third-order step from the hardware's estimate, with the
+// rounding of x y carried along (correct to about half a unit)
+__device__ __forceinline__ double rsqrt_h(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double xy = x * y, lo = fma(x, y, -xy);
+  const double e = fma(-lo, y, fma(-xy, y, 1.0));
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
+// The rotation of make_rot in the shortest chain of dependent operations: with
+// d = b - a, r = sqrt(d^2 + 4 |c|^2), p = |d| + r and y = 1/sqrt(p^2 + 4 |c|^2)
+// (= 1/sqrt(2 r p)): cs = p y, sn ph = 2 c y sign(d), t |c| = 4 |c|^2 r y^2
+// sign(d); cs^2 + |sn|^2 = 1 to the rounding of y alone.
+__device__ __forceinline__ RotS make_rot_s(double a, double b, cplx c) {
+  const double m2 = c.x * c.x + c.y * c.y, d = b - a;
+  const bool on = m2 > 1e-300;
+  const double m4 = 4.0 * m2, q = fma(d, d, m4);
+  const double r = q * rsqrt_h(q), p = fabs(d) + r;
+  const double y = rsqrt_h(fma(p, p, m4)), y2 = copysign(2.0 * y, d);
+  RotS R;
+  R.cs = on ? p * y : 1.0;
+  R.t = on ? (0.5 * m4 * r) * (y * y2) : 0.0;
+  R.s = on ? make_double2(c.x * y2, c.y * y2) : make_double2(0.0, 0.0);
+  return R;
+}
+// LDS: four entry planes of A's blocks and two of V's pairs, twice each
+inline size_t jac_mid_lds(int64_t n) {
+  const size_t h = (size_t)(n + 1) / 2;
+  return 2 * (4 * h * h + 2 * 2 * h * h) * sizeof(cplx);
+}
+
+__device__ __forceinline__ void jacobi_mid_body(int n, const cplx* __restrict__ Ain, int64_t lda,
+                                                double* __restrict__ w, cplx* __restrict__ Q,
+                                                int64_t ldq, int* sweeps_out) {
+  extern __shared__ cplx sm[];
+  __shared__ double red[2][kJacThreads / 64];
+  __shared__ int rank_[kJacMidMax];
+  const int h = (n + 1) / 2, n2 = 2 * h, m = n2 - 1, hh = h * h;
+  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
+  // buffer u: A entry planes e = 2 (row role) + (column role) at e hh, V planes (column
+  // role) at (4 + 2 role) hh, [row][pair]
+  const int bufsz = 8 * hh;
+  // position (role, k) -> index in round 0, and -> position 2 k + role of the next round
+  auto index0 = [&](int role, int k) { return k == 0 ? (role ? 0 : m) : role ? m - k : k; };
+  auto next = [&](int role, int k) {
+    if (role) return k == h - 1 ? 2 * k : 2 * (k + 1) + 1;
+    return k == 0 ? 0 : k == 1 ? 1 : 2 * (k - 1);
+  };
+  const bool own = tid < hh;
+  const int P = own ? tid / h : 0, Qb = own ? tid - P * h : 0;
+  if (own) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = index0(e >> 1, P), j = index0(e & 1, Qb);
+      sm[e * hh + tid] = (i < n && j < n) ? Ain[i + (int64_t)j * lda] : make_double2(0.0, 0.0);
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+        sm[(4 + 2 * c) * hh + (P + g * h) * h + Qb] =
+            make_double2(P + g * h == index0(c, Qb) ? 1.0 : 0.0, 0.0);
+  }
+  // where this thread's results go
+  int dst[4], vdst[2];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int i = h > 1 ? next(e >> 1, P) : e >> 1, j = h > 1 ? next(e & 1, Qb) : e & 1;
+    dst[e] = (2 * (i & 1) + (j & 1)) * hh + (i >> 1) * h + (j >> 1);
+  }
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int j = h > 1 ? next(c, Qb) : c;
+    vdst[c] = (4 + 2 * (j & 1)) * hh + P * h + (j >> 1);
+  }
+  const int dP = P * (h + 1), dQ = Qb * (h + 1);   // the pairs' diagonal blocks
+  __syncthreads();
+  int sweeps = 0, cur = 0;
+  bool done = false;
+  for (; sweeps < kMaxSweeps; ++sweeps) {
+    {
+      const cplx* A = sm + cur * bufsz;
+      double off = 0.0, tot = 0.0;
+      if (own) {
+        const double m11 = cabs2(A[tid]), m12 = cabs2(A[hh + tid]);
+        const double m21 = cabs2(A[2 * hh + tid]), m22 = cabs2(A[3 * hh + tid]);
+        off = m12 + m21;
+        tot = off + m11 + m22;
+        if (P != Qb) off = tot;
+      }
+#pragma unroll
+      for (int s = 32; s > 0; s >>= 1) {
+        off += __shfl_xor(off, s, 64);
+        tot += __shfl_xor(tot, s, 64);
+      }
+      if (lane == 0) {
+        red[0][wave] = off;
+        red[1][wave] = tot;
+      }
+      __syncthreads();
+      // the owners' wavefronts in order: independent of the workgroup's size
+      off = tot = 0.0;
+      for (int q = 0; q < (hh + 63) / 64; ++q) {
+        off += red[0][q];
+        tot += red[1][q];
+      }
+      const double tl = jac_tol(n);
+      done = off <= tl * tl * tot;
+    }
+    if (done) break;
+    for (int r = 0; r < m; ++r) {
+      if (own) {
+        const cplx* A = sm + cur * bufsz;
+        cplx* B = sm + (bufsz - cur * bufsz);
+        const double ap = A[dP].x, aq = A[3 * hh + dP].x, bp = A[dQ].x, bq = A[3 * hh + dQ].x;
+        const cplx cp = A[hh + dP], cq = A[hh + dQ];
+        cplx x11 = A[tid], x12 = A[hh + tid], x21 = A[2 * hh + tid], x22 = A[3 * hh + tid];
+        const cplx* V = A + 4 * hh + tid;
+        const cplx y1 = V[0], y2 = V[2 * hh], z1 = V[hh], z2 = V[3 * hh];
+        const RotS RP = make_rot_s(ap, aq, cp), RQ = make_rot_s(bp, bq, cq);
+        {
+          // M = X Jq, then Jp^H M
+          const cplx q21 = make_double2(-RQ.s.x, RQ.s.y);
+          const cplx m11 = cadd(cscale(x11, RQ.cs), cmul(x12, q21));
+          const cplx m12 = cadd(cmul(x11, RQ.s), cscale(x12, RQ.cs));
+          const cplx m21 = cadd(cscale(x21, RQ.cs), cmul(x22, q21));
+          const cplx m22 = cadd(cmul(x21, RQ.s), cscale(x22, RQ.cs));
+          const cplx p12 = make_double2(-RP.s.x, -RP.s.y), p21 = cconj(RP.s);
+          x11 = cadd(cscale(m11, RP.cs), cmul(p12, m21));
+          x12 = cadd(cscale(m12, RP.cs), cmul(p12, m22));
+          x21 = cadd(cmul(p21, m11), cscale(m21, RP.cs));
+          x22 = cadd(cmul(p21, m12), cscale(m22, RP.cs));
+          if (P == Qb) {
+            x11 = make_double2(ap - RP.t, 0.0);
+            x22 = make_double2(aq + RP.t, 0.0);
+            x12 = x21 = make_double2(0.0, 0.0);
+          }
+          B[dst[0]] = x11;
+          B[dst[1]] = x12;
+          B[dst[2]] = x21;
+          B[dst[3]] = x22;
+          B[vdst[0]] = cadd(cscale(y1, RQ.cs), cmul(y2, q21));
+          B[vdst[0] + hh] = cadd(cscale(z1, RQ.cs), cmul(z2, q21));
+          B[vdst[1]] = cadd(cmul(y1, RQ.s), cscale(y2, RQ.cs));
+          B[vdst[1] + hh] = cadd(cmul(z1, RQ.s), cscale(z2, RQ.cs));
+        }
+      }
+      __syncthreads();
+      cur ^= 1;
+    }
+  }
+  // sort ascending (rank by value, ties by index) and write out
+  const cplx* A = sm + cur * bufsz;
+  // position of index i in round 0: diagonal entry and V column
+  auto role0 = [&](int i) { return i == m || (i > 0 && i < h) ? 0 : 1; };
+  auto pair0 = [&](int i) { return i == m || i == 0 ? 0 : i < h ? i : m - i; };
+  auto diag = [&](int i) { return A[3 * hh * role0(i) + pair0(i) * (h + 1)].x; };
+  for (int i = tid; i < n; i += nt) {
+    const double di = diag(i);
+    int rk = 0;
+    for (int j = 0; j < n; ++j) {
+      const double dj = diag(j);
+      if (dj < di || (dj == di && j < i)) ++rk;
+    }
+    rank_[i] = rk;
+    w[rk] = di;
+  }
+  __syncthreads();
+  for (int idx = tid; idx < n * n; idx += nt) {
+    const int j = idx / n, i = idx - j * n;
+    Q[i + (int64_t)rank_[j] * ldq] = A[(4 + 2 * role0(j)) * hh + i * h + pair0(j)];
+  }
+  if (tid == 0) sweeps_out[0] = done ? sweeps : -1;
+}
+
+// Whole Jacobi solve in LDS for kJacMidMax < n <= 64 (two copies of A and V do
+// not fit the LDS): in place, the rotations of a round formed by h threads.
+__device__ __forceinline__ void jacobi_64_body(int n, const cplx* __restrict__ Ain, int64_t lda, double* __restrict__ w,
                cplx* __restrict__ Q, int64_t ldq, int* sweeps_out) {
   extern __shared__ cplx sm[];
   const int n2 = n + (n & 1);
@@ -555,7 +752,19 @@ __device__ __forceinline__ void jacobi_small_body(int n, const cplx* __restrict_
   if (tid == 0) sweeps_out[0] = done ? sweeps : -1;
 }
 
-__global__ void 
+__device__ __forceinline__ void jacobi_small_body(int n, const cplx* __restrict__ Ain, int64_t lda,
+                                                  double* __restrict__ w, cplx* __restrict__ Q,
+                                                  int64_t ldq, int* sweeps_out) {
+  if (n <= kJacMidMax) jacobi_mid_body(n, Ain, lda, w, Q, ldq, sweeps_out);
+  else jacobi_64_body(n, Ain, lda, w, Q, ldq, sweeps_out);
+}
+// dynamic LDS of solves of up to n
+inline size_t jac_small_lds(int64_t n) {
+  const size_t mid = jac_mid_lds(std::min<int64_t>(n, kJacMidMax));
+  return n > kJacMidMax ? std::max(mid, (size_t)(n * (2 * n + 1)) * sizeof(cplx)) : mid;
+}
+
+__global__ void __launch_bounds__(kJacThreads)
 k_jacobi_small(int n, const cplx* __restrict__ Ain, int64_t lda, double* __restrict__ w,
                cplx* __restrict__ Q, int64_t ldq, int* sweeps_out) {
   jacobi_small_body(n, Ain, lda, w, Q, ldq, sweeps_out);
@@ -1434,7 +1643,7 @@ hipError_t heev_set_lds_limit(size_t bytes) {
 hipError_t launch_heev_small_async(int64_t n, const cplx* a, int64_t lda, double* w, cplx* q,
                                    int64_t ldq, int* sweeps_dev, hipStream_t s) {
   if (n > kJacSmallMax) return hipErrorInvalidValue;
-  const size_t lds = (size_t)(n * (2 * n + 1)) * sizeof(cplx);
+  const size_t lds = jac_small_lds(n);
   hipLaunchKernelGGL(k_jacobi_small, dim3(1), dim3(jac_threads((int)n)), lds, s, (int)n, a, lda, w,
                      q, ldq, sweeps_dev);
   return hipGetLastError();
@@ -1578,7 +1787,7 @@ hipError_t launch_fused_dense(FusedStep step, int nitems, int64_t npw_nb_max, in
       break;
     case FS_JACOBI:
       hipLaunchKernelGGL(kb_jacobi, dim3(nitems), dim3(jac_threads(nb_max)),
-                         (size_t)(nb_max * (2 * nb_max + 1)) * sizeof(cplx), s, D);
+                         jac_small_lds(nb_max), s, D);
       break;
     case FS_RESIDUALS:
       hipLaunchKernelGGL(kb_residuals, dim3(nb_max, nitems), dim3(256), 0, s, D);
