@@ -11,6 +11,7 @@
 #include "fft_common.h"
 
 #include <algorithm>
+#include <type_traits>
 
 using namespace pwfft;
 
@@ -83,15 +84,26 @@ k_col_inv_reg(BoxPlan P, const C* __restrict__ tw3, const S* __restrict__ psi, i
   col_inv_reg_body<N3, C, S>(P, tw3, psi, ldpsi, T, blockIdx.x, blockIdx.y);
 }
 
+// Few projectors (nonlocal_in_columns): P C is added as the points are emitted.
+template <class C>
+struct ColNonlocal {
+  const C* proj;     // npw x n, ld ldp
+  int64_t ldp;
+  const C* c;        // n x nb (scaled projections of the launch's bands)
+  int n;
+};
+struct NoNonlocal {};
+
 // S: storage type of the blocks in, prev and out.
-template <int N3, class C, class S = C>
+template <int N3, class C, class S = C, class NL = NoNonlocal>
 __device__ __forceinline__ void col_fwd_reg_body(const BoxPlan& P, const C* __restrict__ tw3,
                                                  const C* __restrict__ T,
                                                  const real_t<C>* __restrict__ kin, const S* in,
                                                  int64_t ldin, const S* prev, int64_t ldprev,
                                                  S* out, int64_t ldout, double alpha_d,
                                                  double beta_d, double gamma_d,
-                                                 const double* __restrict__ coef, int cb, int b) {
+                                                 const double* __restrict__ coef, int cb, int b,
+                                                 const NL& nl = NL()) {
   using Rl = real_t<C>;
   constexpr int G = lane_group(N3), R = N3 / G, CT = kColThreads / G, TRS = N3 + 1;
   __shared__ C tile[CT * TRS];
@@ -139,6 +151,15 @@ __device__ __forceinline__ void col_fwd_reg_body(const BoxPlan& P, const C* __re
       val.x += gamma * p.x;
       val.y += gamma * p.y;
     }
+    if constexpr (!std::is_same<NL, NoNonlocal>::value) {
+      const C* cj = nl.c + (size_t)b * nl.n;
+#pragma unroll 4
+      for (int j = 0; j < nl.n; ++j) {
+        const C p = nl.proj[g + j * nl.ldp], c = cj[j];
+        val.x += p.x * c.x - p.y * c.y;
+        val.y += p.x * c.y + p.y * c.x;
+      }
+    }
     outb[g] = st_c<S>(val);
   };
   if (P.runs) {
@@ -166,6 +187,17 @@ k_col_fwd_reg(BoxPlan P, const C* __restrict__ tw3, const C* __restrict__ T,
               double gamma_d, const double* __restrict__ coef) {
   col_fwd_reg_body<N3, C, S>(P, tw3, T, kin, in, ldin, prev, ldprev, out, ldout, alpha_d, beta_d,
                              gamma_d, coef, blockIdx.x, blockIdx.y);
+}
+
+template <int N3, class C>
+__global__ void __launch_bounds__(kColThreads)
+k_col_fwd_nl(BoxPlan P, const C* __restrict__ tw3, const C* __restrict__ T,
+             const real_t<C>* __restrict__ kin, const C* in, int64_t ldin, const C* prev,
+             int64_t ldprev, C* out, int64_t ldout, double alpha_d, double beta_d, double gamma_d,
+             const double* __restrict__ coef, ColNonlocal<C> nl) {
+  col_fwd_reg_body<N3, C, C, ColNonlocal<C>>(P, tw3, T, kin, in, ldin, prev, ldprev, out, ldout,
+                                             alpha_d, beta_d, gamma_d, coef, blockIdx.x, blockIdx.y,
+                                             nl);
 }
 
 template <int N1, int N2, int GMAX, class C>
@@ -317,6 +349,20 @@ kb_col_fwd_reg(const ItemDev* __restrict__ D, int sel_in, int sel_out, int sel_p
                           item_block<C>(d, sel_out), d.npw, alpha, beta, gamma,
                           coef_step >= 0 ? d.coef + 3 * coef_step : nullptr, blockIdx.x,
                           blockIdx.y);
+}
+
+template <int N3>
+__global__ void __launch_bounds__(kColThreads)
+kb_col_fwd_nl(const ItemDev* __restrict__ D, int sel_in, int sel_out, int sel_prev, double alpha,
+              double beta, double gamma, int coef_step) {
+  constexpr int CT = kColThreads / lane_group(N3);
+  const ItemDev& d = D[blockIdx.z];
+  if ((int)blockIdx.y >= d.nb || (int)blockIdx.x * CT >= d.plan.ncols) return;
+  const ColNonlocal<double2> nl{d.proj, d.npw, d.cprj, d.nproj};
+  col_fwd_reg_body<N3, double2, double2, ColNonlocal<double2>>(
+      d.plan, d.plan.ax3.tw, d.T, d.kin, item_blk64(d, sel_in), d.npw, item_blk64(d, sel_prev), d.npw,
+      item_blk64(d, sel_out), d.npw, alpha, beta, gamma,
+      coef_step >= 0 ? d.coef + 3 * coef_step : nullptr, blockIdx.x, blockIdx.y, nl);
 }
 
 template <int N1, int N2, int GMAX, class C>
@@ -563,6 +609,39 @@ hipError_t launch_fused_col_fwd_reg(const FusedFft& f, bool fp32, const ItemDev*
                                           coef_step, s)
               : fused_col_fwd_reg<double2>(f, D, sel_in, sel_out, sel_prev, alpha, beta, gamma,
                                            coef_step, s);
+}
+hipError_t launch_fused_col_fwd_nl(const FusedFft& f, const ItemDev* D, int sel_in, int sel_out,
+                                   int sel_prev, double alpha, double beta, double gamma,
+                                   int coef_step, hipStream_t s) {
+#define CASE(N)                                                                                 \
+  if (f.n3 == N) {                                                                              \
+    constexpr int CT = kColThreads / lane_group(N);                                             \
+    dim3 grid((f.ncols_max + CT - 1) / CT, f.nb_max, f.nitems);                                 \
+    hipLaunchKernelGGL(kb_col_fwd_nl<N>, grid, dim3(kColThreads), 0, s, D, sel_in, sel_out,     \
+                       sel_prev, alpha, beta, gamma, coef_step);                                \
+    return hipGetLastError();                                                                   \
+  }
+  PW_FAST_SIZES(CASE)
+#undef CASE
+  return hipErrorInvalidValue;
+}
+hipError_t launch_fft_col_fwd_nl(const BoxPlan& p, int nb, const cplx* T, const double* kin,
+                                 const cplx* in, int64_t ldin, const cplx* prev, int64_t ldprev,
+                                 cplx* out, int64_t ldout, const Epilogue& ep, const cplx* proj,
+                                 int64_t ldp, const cplx* cprj, int nproj, hipStream_t s) {
+  const ColNonlocal<double2> nl{proj, ldp, cprj, nproj};
+#define CASE(N)                                                                                 \
+  if (p.n3 == N) {                                                                              \
+    constexpr int CT = kColThreads / lane_group(N);                                             \
+    dim3 grid((p.ncols + CT - 1) / CT, nb);                                                     \
+    hipLaunchKernelGGL((k_col_fwd_nl<N, double2>), grid, dim3(kColThreads), 0, s, p, p.ax3.tw, T, \
+                       kin, in, ldin, prev, ldprev, out, ldout, ep.alpha, ep.beta, ep.gamma,    \
+                       ep.coef, nl);                                                            \
+    return hipGetLastError();                                                                   \
+  }
+  PW_FAST_SIZES(CASE)
+#undef CASE
+  return hipErrorInvalidValue;
 }
 hipError_t launch_fused_plane_reg(const FusedFft& f, bool fp32, const ItemDev* D, hipStream_t s) {
   return fp32 ? fused_plane_reg<float2>(f, f.plane_variant32, D, s)

@@ -53,6 +53,7 @@ struct pw_batch {
     FusedFft f{};
     ItemDev* D = nullptr;            // device descriptors of the group's items
     int nitems = 0, nb_max = 0, nproj_max = 0;
+    bool few = false;                // FP64 non-local part in the column kernels
     int64_t npw_max = 0, npw_nb_max = 0;
     int nsplit_proj = 1, nsplit_gram = 1, nsplit_proj32 = 1;
   };
@@ -164,6 +165,7 @@ pw_status ham_apply(pw_ham* h, int64_t nb, const cplx* in, int64_t ldin, cplx* o
   // the shape rules
   FftLaunchCfg cfg = h->cfg;
   if (repro) cfg.pq64 = cfg.pq64_sq = false;
+  const bool few = nonlocal_in_columns(h->nproj, h->npw, nb, cfg.reg_col);
   const int target = repro ? gemm_cn_fixed_target(h->gemm_target) : h->gemm_target;
   const bool fork = h->nproj > 0 && c->overlap && c->stream == c->home;
   if (h->nproj > 0) {
@@ -174,9 +176,13 @@ pw_status ham_apply(pw_ham* h, int64_t nb, const cplx* in, int64_t ldin, cplx* o
       HIPCHK(c, hipStreamWaitEvent(ps, c->ev_fork, 0));
     }
     StageScope sc(c, PW_STAGE_PROJ, ps);
-    HIPCHK(c, launch_gemm_cn(h->nproj, nb, h->npw, alpha, h->proj, h->npw, in, ldin, h->cprj,
-                             h->nproj, h->ekb_dev, h->gemm_work, ps, 0.0, coef, target, 0,
-                             craw, h->nproj));
+    if (few)
+      HIPCHK(c, launch_proj_few(h->nproj, nb, h->npw, alpha, coef, h->proj, h->npw, in, ldin, h->cprj,
+                                h->ekb_dev, craw, ps));
+    else
+      HIPCHK(c, launch_gemm_cn(h->nproj, nb, h->npw, alpha, h->proj, h->npw, in, ldin, h->cprj,
+                               h->nproj, h->ekb_dev, h->gemm_work, ps, 0.0, coef, target, 0,
+                               craw, h->nproj));
   }
   if (fork) HIPCHK(c, hipEventRecord(c->ev_join, c->aux));
   const Epilogue ep{alpha, beta, gamma, coef};
@@ -191,14 +197,21 @@ pw_status ham_apply(pw_ham* h, int64_t nb, const cplx* in, int64_t ldin, cplx* o
       HIPCHK(c, launch_fft_plane(h->plan, cfg, nc, h->vscaled, h->T, s));
     }
     {
+      if (few && fork && c0 == 0) HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));
       StageScope sc(c, PW_STAGE_FFT_COL_FWD);
-      HIPCHK(c, launch_fft_col_fwd(h->plan, cfg, nc, h->T, h->kin, in + c0 * ldin, ldin,
+      if (few)
+        HIPCHK(c, launch_fft_col_fwd_nl(h->plan, nc, h->T, h->kin, in + c0 * ldin, ldin,
+                                        prev ? prev + c0 * ldprev : nullptr, ldprev,
+                                        out + c0 * ldout, ldout, ep, h->proj, h->npw,
+                                        h->cprj + c0 * h->nproj, (int)h->nproj, s));
+      else
+        HIPCHK(c, launch_fft_col_fwd(h->plan, cfg, nc, h->T, h->kin, in + c0 * ldin, ldin,
                                    prev ? prev + c0 * ldprev : nullptr, ldprev, out + c0 * ldout,
                                    ldout, ep, s));
     }
   }
-  if (fork) HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));
-  if (h->nproj > 0) {
+  if (fork && !few) HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));
+  if (h->nproj > 0 && !few) {
     StageScope sc(c, PW_STAGE_NONLOCAL);
     HIPCHK(c, launch_gemm_nn(h->npw, nb, h->nproj, 1.0, h->proj, h->npw, h->cprj, h->nproj, 1.0,
                              out, ldout, s, h->nn_tile));
@@ -612,8 +625,9 @@ pw_status fused_setup(pw_batch* b) {
     // share a group, whose LDS is the largest of its items')
     const bool p64 = rp ? h->cfg.pq64_sq : h->cfg.pq64, p32 = rp ? h->cfg.pq32_sq : h->cfg.pq32;
     const bool own = p64 && p32 ? fft_plane_pq_large(h->plan) : rp || p64 || p32;
-    bybox[{rc ? h->plan.n3 : -1, own ? h->plan.n1 : -1, own ? h->plan.n2 : -1, p64, p32}].push_back(
-        (int)i);
+    bybox[{rc ? h->plan.n3 : -1, own ? h->plan.n1 : -1, own ? h->plan.n2 : -1, p64, p32,
+           nonlocal_in_columns(h->nproj, h->npw, b->items[i].nb, rc)}]
+        .push_back((int)i);
   }
   for (auto& kv : bybox) {
     pw_batch::Group g;
@@ -661,6 +675,7 @@ pw_status fused_setup(pw_batch* b) {
     }
     g.nitems = f.nitems;
     g.nb_max = f.nb_max;
+    g.few = nonlocal_in_columns(h0->nproj, h0->npw, b->items[ids[0]].nb, f.reg_col);
     std::vector<ItemDev> host(ids.size());
     for (size_t q = 0; q < ids.size(); ++q) {
       const BatchItem& it = b->items[ids[q]];
@@ -726,9 +741,12 @@ pw_status fused_apply(pw_ctx* c, const pw_batch::Group& g, int prec, int in, int
   const bool lp = prec != PW_FP64;
   const int bf16 = prec == PW_BF16;
   const int lps = lp ? PW_STAGE_FFT_COL_INV_LP - PW_STAGE_FFT_COL_INV : 0;
+  const bool few = g.few && !lp;
   if (g.nproj_max > 0) {
     StageScope sc(c, PW_STAGE_PROJ + lps);
-    if (lp)
+    if (few)
+      HIPCHK(c, launch_fused_proj_few(g.nitems, g.nproj_max, g.nb_max, g.D, in, alpha, coef_step, s));
+    else if (lp)
       HIPCHK(c, launch_fused_gemm_cn32(bf16, g.nitems, g.nproj_max, g.nb_max, g.nsplit_proj32, g.D,
                                        in, alpha, coef_step, s));
     else
@@ -745,9 +763,12 @@ pw_status fused_apply(pw_ctx* c, const pw_batch::Group& g, int prec, int in, int
   }
   {
     StageScope sc(c, PW_STAGE_FFT_COL_FWD + lps);
-    HIPCHK(c, launch_fused_col_fwd(g.f, lp, g.D, in, out, prev, alpha, beta, gamma, coef_step, s));
+    if (few)
+      HIPCHK(c, launch_fused_col_fwd_nl(g.f, g.D, in, out, prev, alpha, beta, gamma, coef_step, s));
+    else
+      HIPCHK(c, launch_fused_col_fwd(g.f, lp, g.D, in, out, prev, alpha, beta, gamma, coef_step, s));
   }
-  if (g.nproj_max > 0) {
+  if (g.nproj_max > 0 && !few) {
     StageScope sc(c, PW_STAGE_NONLOCAL + lps);
     if (lp) HIPCHK(c, launch_fused_gemm_nn32(bf16, g.nitems, g.npw_max, g.nb_max, g.D, out, s));
     else HIPCHK(c, launch_fused_gemm_nn(g.nitems, g.npw_max, g.nb_max, g.D, GOP_NONLOCAL, 0, out, s));
