@@ -347,12 +347,20 @@ __device__ __forceinline__ void rr_pair(int r, int k, int n2, int* p, int* q) {
   *q = max(a, b);
 }
 
+// number of i's pair in round r of the circle method, m = n2 - 1
+__device__ __forceinline__ int rr_slot(int r, int i, int m) {
+  const int k = i < r ? i - r + m : i - r;
+  return (i == m || i == r) ? 0 : min(k, m - k);
+}
+
 // Rotation J = [[cs, sn ph], [-sn conj(ph), cs]] with J^H [[a, c], [conj c, b]] J diagonal:
 // tau = (b - a)/(2|c|), t = sign(tau)/(|tau| + sqrt(1 + tau^2)), cs = 1/sqrt(1+t^2), sn = t cs;
 // new diagonal a - t|c|, b + t|c|.  |c| below 1e-150 (|c|^2 near the
 // denormal range) counts as zero: no rotation.  (Matrix entries here are
 // O(1) Hamiltonian elements.)
-__device__ __forceinline__ Rot make_rot(double a, double b, cplx c) {
+// *tan, *absc: t and |c| unselected, for a diagonal update in one rounding
+__device__ __forceinline__ Rot make_rot(double a, double b, cplx c, double* tan = nullptr,
+                                        double* absc = nullptr) {
   // branch-free (callers form several rotations side by side); a zero c
   // selects the identity at the end (the arithmetic before it may be inf/NaN)
   Rot R;
@@ -371,8 +379,19 @@ __device__ __forceinline__ Rot make_rot(double a, double b, cplx c) {
   R.cs = R.on ? cs : 1.0;
   R.sn = R.on ? t * cs : 0.0;
   R.t = R.on ? t * mag : 0.0;
+  if (tan) *tan = t, *absc = mag;
   R.ph = R.on ? make_double2(c.x * rmag, c.y * rmag) : make_double2(1.0, 0.0);
   return R;
+}
+
+// The products of a rotation with their rounding written out: left to the
+// compiler, which of two products is fused depends on the code around it, and
+// the phases of nearly degenerate vectors follow the last bit.
+__device__ __forceinline__ cplx rmul(cplx a, cplx b) {
+  return make_double2(fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x));
+}
+__device__ __forceinline__ cplx rmac(cplx a, double c, cplx s) {   // a c + s
+  return make_double2(fma(a.x, c, s.x), fma(a.y, c, s.y));
 }
 
 // 2x2 block update X <- Jp^H X Jq, X = [[x11, x12], [x21, x22]]
@@ -381,17 +400,17 @@ __device__ __forceinline__ void rot_block(const Rot& P, const Rot& Q, cplx* x11,
   // M = X Jq: Jq = [[cs, sn ph], [-sn conj(ph), cs]]
   const cplx q12 = cscale(Q.ph, Q.sn);              // sn ph
   const cplx q21 = cscale(cconj(Q.ph), -Q.sn);      // -sn conj(ph)
-  const cplx m11 = cadd(cscale(*x11, Q.cs), cmul(*x12, q21));
-  const cplx m12 = cadd(cmul(*x11, q12), cscale(*x12, Q.cs));
-  const cplx m21 = cadd(cscale(*x21, Q.cs), cmul(*x22, q21));
-  const cplx m22 = cadd(cmul(*x21, q12), cscale(*x22, Q.cs));
+  const cplx m11 = rmac(*x11, Q.cs, rmul(*x12, q21));
+  const cplx m12 = rmac(*x12, Q.cs, rmul(*x11, q12));
+  const cplx m21 = rmac(*x21, Q.cs, rmul(*x22, q21));
+  const cplx m22 = rmac(*x22, Q.cs, rmul(*x21, q12));
   // Jp^H = [[cs, -sn ph], [sn conj(ph), cs]]
   const cplx p12 = cscale(P.ph, -P.sn);
   const cplx p21 = cscale(cconj(P.ph), P.sn);
-  *x11 = cadd(cscale(m11, P.cs), cmul(p12, m21));
-  *x12 = cadd(cscale(m12, P.cs), cmul(p12, m22));
-  *x21 = cadd(cmul(p21, m11), cscale(m21, P.cs));
-  *x22 = cadd(cmul(p21, m12), cscale(m22, P.cs));
+  *x11 = rmac(m11, P.cs, rmul(p12, m21));
+  *x12 = rmac(m12, P.cs, rmul(p12, m22));
+  *x21 = rmac(m21, P.cs, rmul(p21, m11));
+  *x22 = rmac(m22, P.cs, rmul(p21, m12));
 }
 
 // row update [vp, vq] <- [vp, vq] Jq
@@ -399,8 +418,8 @@ __device__ __forceinline__ void rot_row(const Rot& Q, cplx* vp, cplx* vq) {
   const cplx q12 = cscale(Q.ph, Q.sn);
   const cplx q21 = cscale(cconj(Q.ph), -Q.sn);
   const cplx a = *vp, b = *vq;
-  *vp = cadd(cscale(a, Q.cs), cmul(b, q21));
-  *vq = cadd(cmul(a, q12), cscale(b, Q.cs));
+  *vp = rmac(a, Q.cs, rmul(b, q21));
+  *vq = rmac(b, Q.cs, rmul(a, q12));
 }
 
 constexpr int kJacSmallMax = 64;
@@ -796,87 +815,151 @@ __device__ __forceinline__ int bj_index(int i, int I, int J) {
 
 // One sweep on each block pair of outer round r (workgroup k: pair k);
 // Qout[k] (kBJS x kBJS, column-major) receives the accumulated rotations.
-// One thread per 2x2 block of A (kBJ^2 blocks: thread (P, Qb) takes rows
-// of pair P and columns of pair Qb of the inner round) and per two (row,
-// pair) items of V (rows Qb and Qb + kBJ, pair P).  A is double-buffered:
-// each inner round reads one copy and writes the other, so every thread
-// forms the two rotations it needs from the entries it reads (the same
-// arithmetic on the same values in every thread that forms one) and an
-// inner round needs a single barrier.  a0 holds the sub-problem on entry
-// (ld kBJS + 1); a1 and v are LDS of the same size.
-constexpr int kBJInnerThreads = kBJ * kBJ;
-constexpr int kBJLA = kBJS + 1;           // ld of the sub-problem (odd: spreads the LDS banks)
-static_assert(2 * kBJInnerThreads == kBJS * kBJ, "V (row, pair) items: two per thread");
+//
+// An inner round is a chain of dependent steps with one barrier, and a
+// wavefront issues an instruction about every five cycles, so the instructions
+// of the wavefronts on that chain are its time.  Wavefronts 0 .. 3 hold one 2x2
+// block of A per thread: thread (P, Qb) has rows of pair P and columns of pair
+// Qb.  A is kept by pair position, the lower index of pair k at 2 k and the
+// higher at 2 k + 1, in four planes (row and column position even or odd), so
+// every round reads the same addresses; where the results stand in the next
+// round comes from a table.  Every thread forms the rotation of pair Qb and
+// takes pair P's from lane P of its wavefront.  A is double-buffered.
+// Wavefronts 4 .. 7 apply the previous round's rotations, which the first ones
+// leave in LDS, to V (rows Qb and Qb + kBJ of pair P).  With V, and the circle
+// method's index arithmetic, on the chain's own wavefronts a sweep of 31 rounds
+// took 31.4 us (k_bj_inner) and a fused step 40.4 us at n = 160 and 45.5 us at
+// n = 448; as it is, 24.2, 32.2 and 36.6 us.
+constexpr int kBJHalf = kBJ * kBJ;               // threads of the A part
+constexpr int kBJThreads = 2 * kBJHalf;
+constexpr int kBJA = 4 * kBJHalf;                // entries of one copy of A
+static_assert(2 * kBJHalf == kBJS * kBJ, "V (row, pair) items: two per thread");
 static_assert(64 % kBJ == 0, "the lanes P < kBJ of every wavefront hold the pairs' rotations");
-__device__ __forceinline__ void bj_inner_sweep(cplx* a0, cplx* a1, cplx* v, cplx* __restrict__ qo) {
-  constexpr int LA = kBJLA;
+// offsets of a row and of a column position in the planes
+__host__ __device__ constexpr int bj_rowpart(int pos) { return (pos & 1) * 2 * kBJHalf + (pos >> 1) * kBJ; }
+__host__ __device__ constexpr int bj_colpart(int pos) { return (pos & 1) * kBJHalf + (pos >> 1); }
+// Per round and pair: the pair's indices, and the row and column offsets of
+// their positions in the next round.
+struct BjTable {
+  unsigned pq[kBJS - 1][kBJ], row[kBJS - 1][kBJ], col[kBJS - 1][kBJ];   // low half: lower index
+};
+constexpr BjTable bj_make_table() {
+  BjTable t{};
+  constexpr int m = kBJS - 1;
+  int lo[kBJS][kBJ] = {}, hi[kBJS][kBJ] = {}, pos[kBJS][kBJS] = {};
+  for (int r = 0; r <= m; ++r)
+    for (int k = 0; k < kBJ; ++k) {
+      const int a = k == 0 ? m : (r % m + k) % m, b = k == 0 ? r % m : (r % m - k + m) % m;
+      lo[r][k] = a < b ? a : b;
+      hi[r][k] = a < b ? b : a;
+      pos[r][lo[r][k]] = 2 * k;
+      pos[r][hi[r][k]] = 2 * k + 1;
+    }
+  for (int r = 0; r < m; ++r)
+    for (int k = 0; k < kBJ; ++k) {
+      const int p = pos[r + 1][lo[r][k]], q = pos[r + 1][hi[r][k]];
+      t.pq[r][k] = lo[r][k] | hi[r][k] << 16;
+      t.row[r][k] = bj_rowpart(p) | bj_rowpart(q) << 16;
+      t.col[r][k] = bj_colpart(p) | bj_colpart(q) << 16;
+    }
+  return t;
+}
+__device__ const BjTable bj_table = bj_make_table();
+// position of index i in round 0: pairs (k, 31 - k), and (0, 31) for k = 0
+__device__ __forceinline__ int bj_pos0(int i) { return i < kBJ ? 2 * i : 2 * (kBJS - 1 - i) + 1; }
+__device__ __forceinline__ int bj_place0(int i, int j) {
+  return bj_rowpart(bj_pos0(i)) + bj_colpart(bj_pos0(j));
+}
+
+// LDS beside the two copies of A: V, two rounds of rotations, the table
+struct BjSweepLds {
+  cplx v[kBJS * kBJS];
+  Rot rots[2][kBJ];
+  BjTable tab;
+};
+// a0: the sub-problem on entry, entry (i, j) at bj_place0(i, j)
+__device__ __forceinline__ void bj_inner_sweep(cplx* a0, cplx* a1, BjSweepLds* L,
+                                               cplx* __restrict__ qo) {
   const int tid = threadIdx.x;
-  for (int idx = tid; idx < kBJS * kBJS; idx += kBJInnerThreads) {
+  cplx* v = L->v;
+  for (int idx = tid; idx < kBJS * kBJS; idx += kBJThreads) {
     const int j = idx / kBJS, i = idx - j * kBJS;
     v[idx] = make_double2(i == j ? 1.0 : 0.0, 0.0);
   }
+  for (int idx = tid; idx < (int)(sizeof(BjTable) / 4); idx += kBJThreads)
+    reinterpret_cast<unsigned*>(&L->tab)[idx] = reinterpret_cast<const unsigned*>(&bj_table)[idx];
   __syncthreads();
-  const int P = tid / kBJ, Qb = tid - P * kBJ;
-  for (int rr = 0; rr < kBJS - 1; ++rr) {
-    const cplx* ac = rr & 1 ? a1 : a0;
-    cplx* an = rr & 1 ? a0 : a1;
-    int p1, q1, p2, q2;
-    rr_pair(rr, P, kBJS, &p1, &q1);
-    rr_pair(rr, Qb, kBJS, &p2, &q2);
-    // every thread forms the rotation of its pair Qb; RP (pair P) comes from
-    // lane P of the same wavefront (its Qb is P)
-    const Rot RQ = make_rot(ac[p2 + p2 * LA].x, ac[q2 + q2 * LA].x, ac[p2 + q2 * LA]);
-    Rot RP;
-    RP.cs = __shfl(RQ.cs, P, 64);
-    RP.sn = __shfl(RQ.sn, P, 64);
-    RP.t = __shfl(RQ.t, P, 64);
-    RP.ph = make_double2(__shfl(RQ.ph.x, P, 64), __shfl(RQ.ph.y, P, 64));
-    RP.on = __shfl((int)RQ.on, P, 64) != 0;
-    cplx x11 = ac[p1 + p2 * LA], x12 = ac[p1 + q2 * LA];
-    cplx x21 = ac[q1 + p2 * LA], x22 = ac[q1 + q2 * LA];
-    // an identity rotation (pair off) leaves the values unchanged exactly;
-    // the diagonal block reads RQ (= RP there), so both are formed up front
-    if (P == Qb) {
-      if (RQ.on) {
-        x11 = make_double2(x11.x - RQ.t, 0.0);
-        x22 = make_double2(x22.x + RQ.t, 0.0);
-        x12 = make_double2(0.0, 0.0);
-        x21 = make_double2(0.0, 0.0);
-      }
-    } else {
-      rot_block(RP, RQ, &x11, &x12, &x21, &x22);
-    }
-    an[p1 + p2 * LA] = x11;
-    an[p1 + q2 * LA] = x12;
-    an[q1 + p2 * LA] = x21;
-    an[q1 + q2 * LA] = x22;
+  const bool apart = tid < kBJHalf;
+  const int P = (tid % kBJHalf) / kBJ, Qb = tid % kBJ;
+  // V of round rr: rows Qb, Qb + kBJ of pair P
+  auto v_round = [&](int rr) {
+    const Rot R = L->rots[rr & 1][P];
+    const unsigned pq = L->tab.pq[rr][P];
+    const int p = pq & 0xffff, q = pq >> 16;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int vi = Qb + h * kBJ;
-      cplx x1 = v[vi + p1 * kBJS], x2 = v[vi + q1 * kBJS];
-      rot_row(RP, &x1, &x2);
-      v[vi + p1 * kBJS] = x1;
-      v[vi + q1 * kBJS] = x2;
+      cplx x1 = v[vi + p * kBJS], x2 = v[vi + q * kBJS];
+      rot_row(R, &x1, &x2);
+      v[vi + p * kBJS] = x1;
+      v[vi + q * kBJS] = x2;
+    }
+  };
+  for (int rr = 0; rr < kBJS - 1; ++rr) {
+    if (apart) {
+      const cplx* ac = rr & 1 ? a1 : a0;
+      cplx* an = rr & 1 ? a0 : a1;
+      const int dg = Qb * (kBJ + 1);
+      double tq, cq;
+      const Rot RQ = make_rot(ac[dg].x, ac[3 * kBJHalf + dg].x, ac[kBJHalf + dg], &tq, &cq);
+      Rot RP;
+      RP.cs = __shfl(RQ.cs, P, 64);
+      RP.sn = __shfl(RQ.sn, P, 64);
+      RP.ph = make_double2(__shfl(RQ.ph.x, P, 64), __shfl(RQ.ph.y, P, 64));
+      if (P == 0) L->rots[rr & 1][Qb] = RQ;
+      cplx x11 = ac[tid], x12 = ac[kBJHalf + tid];
+      cplx x21 = ac[2 * kBJHalf + tid], x22 = ac[3 * kBJHalf + tid];
+      const unsigned row = L->tab.row[rr][P], col = L->tab.col[rr][Qb];
+      // an identity rotation (pair off) leaves the values unchanged exactly
+      if (P == Qb) {
+        if (RQ.on) {
+          x11 = make_double2(fma(-cq, tq, x11.x), 0.0);
+          x22 = make_double2(fma(cq, tq, x22.x), 0.0);
+          x12 = make_double2(0.0, 0.0);
+          x21 = make_double2(0.0, 0.0);
+        }
+      } else {
+        rot_block(RP, RQ, &x11, &x12, &x21, &x22);
+      }
+      const int r1 = row & 0xffff, r2 = row >> 16, c1 = col & 0xffff, c2 = col >> 16;
+      an[r1 + c1] = x11;
+      an[r1 + c2] = x12;
+      an[r2 + c1] = x21;
+      an[r2 + c2] = x22;
+    } else if (rr > 0) {
+      v_round(rr - 1);
     }
     __syncthreads();
   }
-  for (int idx = tid; idx < kBJS * kBJS; idx += kBJInnerThreads) qo[idx] = v[idx];
+  if (!apart) v_round(kBJS - 2);
+  __syncthreads();
+  for (int idx = tid; idx < kBJS * kBJS; idx += kBJThreads) qo[idx] = v[idx];
 }
 
 // Round 0 of a sweep: the sub-problems read straight from A.
-__global__ void __launch_bounds__(kBJInnerThreads)
+__global__ void __launch_bounds__(kBJThreads)
 k_bj_inner(int n2p, int r, const cplx* __restrict__ A, cplx* __restrict__ Qout,
            const int* __restrict__ conv) {
   if (conv[0]) return;
-  __shared__ cplx a[2][kBJS * kBJLA];
-  __shared__ cplx v[kBJS * kBJS];
+  __shared__ cplx a[2][kBJA];
+  __shared__ BjSweepLds lds;
   int I, J;
   rr_pair(r, blockIdx.x, n2p / kBJ, &I, &J);
-  for (int idx = threadIdx.x; idx < kBJS * kBJS; idx += kBJInnerThreads) {
+  for (int idx = threadIdx.x; idx < kBJS * kBJS; idx += kBJThreads) {
     const int j = idx / kBJS, i = idx - j * kBJS;
-    a[0][i + j * kBJLA] = A[bj_index(i, I, J) + (int64_t)bj_index(j, I, J) * n2p];
+    a[0][bj_place0(i, j)] = A[bj_index(i, I, J) + (int64_t)bj_index(j, I, J) * n2p];
   }
-  bj_inner_sweep(a[0], a[1], v, Qout + (int64_t)blockIdx.x * kBJS * kBJS);
+  bj_inner_sweep(a[0], a[1], &lds, Qout + (int64_t)blockIdx.x * kBJS * kBJS);
 }
 
 // Two-sided update of outer round r.  Workgroup w < npair^2 takes the
@@ -886,8 +969,7 @@ k_bj_inner(int n2p, int r, const cplx* __restrict__ A, cplx* __restrict__ Qout,
 // of V from row t kBJTile: V[rows, idx_q] <- V[rows, idx_q] Q_q.  Each
 // workgroup reads and writes only its own elements, so Ain may be Aout.
 // sm: LDS of kBJUpdateSm entries.
-constexpr int kBJUThreads = 256;
-static_assert(kBJUThreads == kBJInnerThreads, "fused step: one workgroup size");
+constexpr int kBJUThreads = kBJThreads;
 constexpr int kBJUSmA = (kBJS + 1) * kBJS + 2 * kBJS * kBJS, kBJUSmV = kBJTile * kBJS + kBJS * kBJS;
 constexpr int kBJUpdateSm = kBJUSmA > kBJUSmV ? kBJUSmA : kBJUSmV;
 __device__ __forceinline__ void bj_update_body(int n, int n2p, int r, const cplx* Ain, cplx* Aout,
@@ -1013,18 +1095,13 @@ __device__ __forceinline__ void bj_lookahead(int n2p, int r, int I, int J, const
   constexpr int LX = kBJS + 1, LT = kBJ;
   const int tid = threadIdx.x;
   const int nblk = n2p / kBJ, npair = nblk / 2;
-  int p1 = 0, o1 = 0, p2 = 0, o2 = 0;
-  for (int k = 0; k < npair; ++k) {
-    int Ik, Jk;
-    rr_pair(r - 1, k, nblk, &Ik, &Jk);
-    if (Ik == I) { p1 = k; o1 = 0; }
-    if (Jk == I) { p1 = k; o1 = kBJ; }
-    if (Ik == J) { p2 = k; o2 = 0; }
-    if (Jk == J) { p2 = k; o2 = kBJ; }
-  }
+  // the round-(r-1) pairs of blocks I and J, and which of the pair they are
+  const int m = nblk - 1;
+  const int p1 = rr_slot(r - 1, I, m), p2 = rr_slot(r - 1, J, m);
   int I1, J1, I2, J2;
   rr_pair(r - 1, p1, nblk, &I1, &J1);
   rr_pair(r - 1, p2, nblk, &I2, &J2);
+  const int o1 = I1 == I ? 0 : kBJ, o2 = I2 == J ? 0 : kBJ;
   cplx* X = sm;                         // [i + j LX]: a kBJS x kBJS block of Min
   cplx* L1 = X + LX * kBJS;             // [a + m kBJ] = conj(Q_p1(m, o1 + a))
   cplx* L2 = L1 + kBJS * kBJ;           // the same for p2
@@ -1036,7 +1113,7 @@ __device__ __forceinline__ void bj_lookahead(int n2p, int r, int I, int J, const
   // three blocks: (I, I) from (p1, p1), (I, J) from (p1, p2), (J, J) from
   // (p2, p2); each block's entries are loaded into registers while the
   // previous block's products run
-  constexpr int NX = kBJS * kBJS / kBJInnerThreads;
+  constexpr int NX = kBJS * kBJS / kBJThreads;
   typedef double dv2 __attribute__((ext_vector_type(2)));   // native vector: stays in registers
   dv2 xr[NX];
   auto load_x = [&](int blk) {
@@ -1044,13 +1121,13 @@ __device__ __forceinline__ void bj_lookahead(int n2p, int r, int I, int J, const
     const int Ic = blk == 0 ? I1 : I2, Jc = blk == 0 ? J1 : J2;     // column pair
 #pragma unroll
     for (int t = 0; t < NX; ++t) {
-      const int idx = tid + t * kBJInnerThreads;
+      const int idx = tid + t * kBJThreads;
       const int j = idx / kBJS, i = idx - j * kBJS;
       xr[t] = *reinterpret_cast<const dv2*>(Min + bj_index(i, Ir, Jr) + (int64_t)bj_index(j, Ic, Jc) * n2p);
     }
   };
   load_x(0);
-  for (int idx = tid; idx < kBJS * kBJ; idx += kBJInnerThreads) {
+  for (int idx = tid; idx < kBJS * kBJ; idx += kBJThreads) {
     const int b = idx / kBJS, m = idx - b * kBJS;
     const cplx v1 = q1[m + (o1 + b) * kBJS], v2 = q2[m + (o2 + b) * kBJS];
     R1[idx] = v1;
@@ -1065,30 +1142,26 @@ __device__ __forceinline__ void bj_lookahead(int n2p, int r, int I, int J, const
     __syncthreads();   // X and T free (previous block done; Q copies stored)
 #pragma unroll
     for (int t = 0; t < NX; ++t) {
-      const int idx = tid + t * kBJInnerThreads;
+      const int idx = tid + t * kBJThreads;
       const int j = idx / kBJS, i = idx - j * kBJS;
       X[i + j * LX] = make_double2(xr[t].x, xr[t].y);
     }
     if (blk < 2) load_x(blk + 1);
     __syncthreads();
-    {   // T = L X: kBJ x kBJS, two entries per thread
-      const int a = tid % kBJ, j0 = tid / kBJ;
-      cplx acc[2] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
+    {   // T = L X: kBJ x kBJS, one entry per thread
+      const int a = tid % kBJ, j = tid / kBJ;
+      cplx acc = make_double2(0.0, 0.0);
 #pragma unroll 8
       for (int m = 0; m < kBJS; ++m) {
         const cplx qh = L[a + m * kBJ];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const cplx x = X[m + (j0 + t * kBJ) * LX];
-          acc[t].x += qh.x * x.x - qh.y * x.y;
-          acc[t].y += qh.x * x.y + qh.y * x.x;
-        }
+        const cplx x = X[m + j * LX];
+        acc.x += qh.x * x.x - qh.y * x.y;
+        acc.y += qh.x * x.y + qh.y * x.x;
       }
-#pragma unroll
-      for (int t = 0; t < 2; ++t) T[a + (j0 + t * kBJ) * LT] = acc[t];
+      T[a + j * LT] = acc;
     }
     __syncthreads();
-    {   // S = T R: kBJ x kBJ, one entry per thread
+    if (tid < kBJHalf) {   // S = T R: kBJ x kBJ, one entry per thread
       const int a = tid % kBJ, b = tid / kBJ;
       cplx acc = make_double2(0.0, 0.0);
 #pragma unroll 8
@@ -1098,8 +1171,8 @@ __device__ __forceinline__ void bj_lookahead(int n2p, int r, int I, int J, const
         acc.x += x.x * qv.x - x.y * qv.y;
         acc.y += x.x * qv.y + x.y * qv.x;
       }
-      a0[(da + a) + (db + b) * kBJLA] = acc;
-      if (blk == 1) a0[(db + b) + (da + a) * kBJLA] = cconj(acc);
+      a0[bj_place0(da + a, db + b)] = acc;
+      if (blk == 1) a0[bj_place0(db + b, da + a)] = cconj(acc);
     }
   }
   __syncthreads();
@@ -1112,8 +1185,9 @@ __device__ __forceinline__ void bj_lookahead(int n2p, int r, int I, int J, const
 // the update of round r - 1 from Ain into Aout (and V) with Qin.  The two
 // kinds read the same inputs and write disjoint outputs, so the update of
 // one round runs beside the inner sweep of the next.
-constexpr int kBJStepSm = kBJUpdateSm > kBJLA * kBJS + kBJLookSm ? kBJUpdateSm : kBJLA * kBJS + kBJLookSm;
-static_assert(kBJLookSm >= kBJLA * kBJS + kBJS * kBJS, "the inner sweep's a1 and v fit the scratch");
+constexpr int kBJSweepSm = 2 * kBJA + (int)((sizeof(BjSweepLds) + sizeof(cplx) - 1) / sizeof(cplx));
+constexpr int kBJInnerSm = kBJA + kBJLookSm > kBJSweepSm ? kBJA + kBJLookSm : kBJSweepSm;
+constexpr int kBJStepSm = kBJUpdateSm > kBJInnerSm ? kBJUpdateSm : kBJInnerSm;
 __global__ void __launch_bounds__(kBJUThreads)
 k_bj_step(int n, int n2p, int r, const cplx* __restrict__ Ain, cplx* __restrict__ Aout,
           cplx* __restrict__ V, const cplx* __restrict__ Qin, cplx* __restrict__ Qout,
@@ -1128,9 +1202,10 @@ k_bj_step(int n, int n2p, int r, const cplx* __restrict__ Ain, cplx* __restrict_
   int I, J;
   rr_pair(r, blockIdx.x, n2p / kBJ, &I, &J);
   cplx* a0 = sm;
-  cplx* scr = sm + kBJLA * kBJS;
-  bj_lookahead(n2p, r, I, J, Ain, Qin, a0, scr);
-  bj_inner_sweep(a0, scr, scr + kBJLA * kBJS, Qout + (int64_t)blockIdx.x * kBJS * kBJS);
+  cplx* scr = sm + kBJA;
+  bj_lookahead(n2p, r, I, J, Ain, Qin, a0, scr);   // ends with a barrier: scr is free
+  bj_inner_sweep(a0, scr, reinterpret_cast<BjSweepLds*>(scr + kBJA),
+                 Qout + (int64_t)blockIdx.x * kBJS * kBJS);
 }
 
 // A0 = [a 0; 0 0] (n2 x n2), V0 = [I 0] (n x n2)
@@ -1685,7 +1760,7 @@ hipError_t launch_heev_async(int64_t n, const cplx* a, int64_t lda, double* w, c
     if (sw == max_sweeps) break;
     // round 0 from A; rounds 1 .. nblk - 2 each beside the previous round's
     // update (A -> A1 -> A ...: nblk - 2 copies, even); the last update in place
-    hipLaunchKernelGGL(k_bj_inner, dim3(npair), dim3(kBJInnerThreads), 0, s, (int)n2p, 0,
+    hipLaunchKernelGGL(k_bj_inner, dim3(npair), dim3(kBJThreads), 0, s, (int)n2p, 0,
                        (const cplx*)A, Q0, (const int*)conv);
     cplx* cur = A;
     cplx* nxt = A1;
