@@ -19,14 +19,15 @@ namespace {
 
 constexpr int kColThreads = 256;
 constexpr int kPlaneMaxThreads = 512;
+constexpr int col_tile(int n3) { return kColThreads / lane_group(n3) * (n3 + 1); }
 
-// S: storage type of the block psi (C, or bf16 pairs widened on load).
+// S: storage type of the block psi (C, or bf16 pairs widened on load); tile:
+// LDS of col_tile(N3) entries.
 template <int N3, class C, class S = C>
 __device__ __forceinline__ void col_inv_reg_body(const BoxPlan& P, const C* __restrict__ tw3,
                                                  const S* __restrict__ psi, int64_t ldpsi,
-                                                 C* __restrict__ T, int cb, int b) {
+                                                 C* __restrict__ T, int cb, int b, C* tile) {
   constexpr int G = lane_group(N3), R = N3 / G, CT = kColThreads / G, TRS = N3 + 1;
-  __shared__ C tile[CT * TRS];
   const int c0 = cb * CT;
   const int ncl = min(CT, P.ncols - c0);
   const S* src = psi + (size_t)b * ldpsi;
@@ -81,7 +82,111 @@ template <int N3, class C, class S = C>
 __global__ void __launch_bounds__(kColThreads)
 k_col_inv_reg(BoxPlan P, const C* __restrict__ tw3, const S* __restrict__ psi, int64_t ldpsi,
               C* __restrict__ T) {
-  col_inv_reg_body<N3, C, S>(P, tw3, psi, ldpsi, T, blockIdx.x, blockIdx.y);
+  __shared__ C tile[col_tile(N3)];
+  col_inv_reg_body<N3, C, S>(P, tw3, psi, ldpsi, T, blockIdx.x, blockIdx.y, tile);
+}
+
+// ---- P^H psi for few projectors and plane waves (nonlocal_in_columns): one
+// workgroup forms kFewProj rows of one band's column of C, every thread a
+// slice of the plane waves, kFewUnroll of them loaded at once, so there are no
+// partials to reduce.  Bound by the latency of its loads: 8 x 16 outputs over
+// 1189 values 10.5 + 3.7 us as split product and reduction, 2.7 here.  Four rows
+// per workgroup: eight take 3.7 us, two the same as four but 23 instead of 21
+// us for 576 bands of 3001 values; the sums over lanes go through LDS (by
+// shuffles 3.0 us).
+constexpr int kFewProj = 4, kFewThreads = 256, kFewUnroll = 3;
+constexpr int kFewLds = 2 * kFewProj * (kFewThreads / 64) * 66;   // doubles
+__device__ __forceinline__ void proj_few_body(double* lds, int M, int K, const double* __restrict__ rowscale,
+                                              double alpha, const cplx* __restrict__ A, int64_t lda,
+                                              const cplx* __restrict__ x, cplx* __restrict__ C,
+                                              cplx* __restrict__ Craw, int j0) {
+  constexpr int W = kFewThreads / 64, V = 2 * kFewProj, L = 64 / V;   // L lanes add up a value
+  double(*buf)[V][65] = reinterpret_cast<double(*)[V][65]>(lds);
+  double(*part)[V] = reinterpret_cast<double(*)[V]>(lds + W * V * 65);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nj = min(kFewProj, M - j0);
+  const double rs = rowscale && tid < nj ? rowscale[j0 + tid] : 1.0;
+  const cplx* a[kFewProj];
+#pragma unroll
+  for (int j = 0; j < kFewProj; ++j) a[j] = A + (j0 + min(j, nj - 1)) * lda;   // rows past M: not stored
+  double acc[V];
+#pragma unroll
+  for (int q = 0; q < V; ++q) acc[q] = 0.0;
+  for (int g0 = tid; g0 < K; g0 += kFewThreads * kFewUnroll) {
+    double2 v[kFewUnroll], p[kFewUnroll][kFewProj];
+#pragma unroll
+    for (int u = 0; u < kFewUnroll; ++u) {
+      const int g = min(g0 + u * kFewThreads, K - 1);
+      v[u] = x[g];
+#pragma unroll
+      for (int j = 0; j < kFewProj; ++j) p[u][j] = a[j][g];
+    }
+#pragma unroll
+    for (int u = 0; u < kFewUnroll; ++u) {
+      if (u > 0 && g0 + u * kFewThreads >= K) break;
+#pragma unroll
+      for (int j = 0; j < kFewProj; ++j) {
+        acc[2 * j] += p[u][j].x * v[u].x + p[u][j].y * v[u].y;
+        acc[2 * j + 1] += p[u][j].x * v[u].y - p[u][j].y * v[u].x;
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < V; ++q) buf[wave][q][lane] = acc[q];
+  __syncthreads();
+  double s = 0.0;
+#pragma unroll
+  for (int i = 0; i < V; ++i) s += buf[wave][lane / L][(lane % L) * V + i];
+#pragma unroll
+  for (int t = L / 2; t > 0; t >>= 1) s += __shfl_xor(s, t, 64);
+  if (lane % L == 0) part[wave][lane / L] = s;
+  __syncthreads();
+  if (tid < nj) {
+    double re = 0.0, im = 0.0;
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+      re += part[q][2 * tid];
+      im += part[q][2 * tid + 1];
+    }
+    C[j0 + tid] = make_double2(alpha * rs * re, alpha * rs * im);
+    if (Craw) Craw[j0 + tid] = make_double2(alpha * re, alpha * im);
+  }
+}
+
+// Both readers of psi in one launch (nonlocal_in_columns): workgroups
+// x < ceil(M / kFewProj) form rows of P^H psi, the others transform columns.
+// Either half is a few us of latency, and a second launch beside the first
+// costs more than it hides.
+struct FewProj {
+  const cplx* proj;              // npw x n, ld npw
+  const double* rowscale;
+  const double* alpha_dev;       // overrides alpha when set
+  double alpha;
+  cplx *c, *craw;                // n x nb; craw may be null
+  int n, npw;
+};
+inline int few_blocks(int64_t nproj) { return (int)((nproj + kFewProj - 1) / kFewProj); }
+
+template <int N3>
+union ColFewLds {
+  double2 tile[col_tile(N3)];
+  double few[kFewLds];
+  __device__ ColFewLds() {}
+};
+
+template <int N3>
+__global__ void __launch_bounds__(kColThreads)
+k_col_inv_proj(BoxPlan P, const double2* __restrict__ tw3, const double2* __restrict__ psi,
+               int64_t ldpsi, double2* __restrict__ T, FewProj f) {
+  __shared__ ColFewLds<N3> lds;
+  const int nf = (f.n + kFewProj - 1) / kFewProj, b = blockIdx.y;
+  if ((int)blockIdx.x < nf) {
+    proj_few_body(lds.few, f.n, f.npw, f.rowscale, f.alpha_dev ? f.alpha_dev[0] : f.alpha, f.proj,
+                  f.npw, psi + b * ldpsi, f.c + (int64_t)b * f.n,
+                  f.craw ? f.craw + (int64_t)b * f.n : nullptr, blockIdx.x * kFewProj);
+    return;
+  }
+  col_inv_reg_body<N3, double2>(P, tw3, psi, ldpsi, T, blockIdx.x - nf, b, lds.tile);
 }
 
 // Few projectors (nonlocal_in_columns): P C is added as the points are emitted.
@@ -333,8 +438,31 @@ kb_col_inv_reg(const ItemDev* __restrict__ D, int sel_in) {
   constexpr int CT = kColThreads / lane_group(N3);
   const ItemDev& d = D[blockIdx.z];
   if ((int)blockIdx.y >= d.nb || (int)blockIdx.x * CT >= d.plan.ncols) return;
+  __shared__ C tile[col_tile(N3)];
   col_inv_reg_body<N3, C>(d.plan, tw_of<C>(d.plan.ax3), item_block<C>(d, sel_in), d.npw,
-                          item_T<C>(d), blockIdx.x, blockIdx.y);
+                          item_T<C>(d), blockIdx.x, blockIdx.y, tile);
+}
+
+// k_col_inv_proj over items: nf workgroups in front for the projections
+template <int N3>
+__global__ void __launch_bounds__(kColThreads)
+kb_col_inv_proj(const ItemDev* __restrict__ D, int nf, int sel_in, double alpha, int coef_step) {
+  constexpr int CT = kColThreads / lane_group(N3);
+  __shared__ ColFewLds<N3> lds;
+  const ItemDev& d = D[blockIdx.z];
+  const int b = blockIdx.y, x = (int)blockIdx.x - nf;
+  if (b >= d.nb) return;
+  if (x < 0) {
+    if ((int)blockIdx.x * kFewProj >= d.nproj) return;
+    if (coef_step >= 0) alpha = d.coef[3 * coef_step];
+    proj_few_body(lds.few, d.nproj, d.npw, d.ekb, alpha, d.proj, d.npw,
+                  item_blk64(d, sel_in) + (int64_t)b * d.npw, d.cprj + (int64_t)b * d.nproj, nullptr,
+                  blockIdx.x * kFewProj);
+    return;
+  }
+  if (x * CT >= d.plan.ncols) return;
+  col_inv_reg_body<N3, double2>(d.plan, d.plan.ax3.tw, item_blk64(d, sel_in), d.npw, d.T, x, b,
+                                lds.tile);
 }
 
 template <int N3, class C>
@@ -609,6 +737,38 @@ hipError_t launch_fused_col_fwd_reg(const FusedFft& f, bool fp32, const ItemDev*
                                           coef_step, s)
               : fused_col_fwd_reg<double2>(f, D, sel_in, sel_out, sel_prev, alpha, beta, gamma,
                                            coef_step, s);
+}
+hipError_t launch_fft_col_inv_proj(const BoxPlan& p, int nb, const cplx* psi, int64_t ldpsi, cplx* T,
+                                   double alpha, const double* alpha_dev, const cplx* proj,
+                                   int64_t nproj, int64_t npw, const double* rowscale, cplx* c,
+                                   cplx* craw, hipStream_t s) {
+  const FewProj few{proj, rowscale, alpha_dev, alpha, c, craw, (int)nproj, (int)npw};
+#define CASE(N)                                                                                 \
+  if (p.n3 == N) {                                                                              \
+    constexpr int CT = kColThreads / lane_group(N);                                             \
+    dim3 grid(few_blocks(nproj) + (p.ncols + CT - 1) / CT, nb);                                 \
+    hipLaunchKernelGGL(k_col_inv_proj<N>, grid, dim3(kColThreads), 0, s, p, p.ax3.tw, psi,      \
+                       ldpsi, T, few);                                                          \
+    return hipGetLastError();                                                                   \
+  }
+  PW_FAST_SIZES(CASE)
+#undef CASE
+  return hipErrorInvalidValue;
+}
+hipError_t launch_fused_col_inv_proj(const FusedFft& f, int64_t nproj_max, const ItemDev* D,
+                                     int sel_in, double alpha, int coef_step, hipStream_t s) {
+  const int nf = few_blocks(nproj_max);
+#define CASE(N)                                                                                 \
+  if (f.n3 == N) {                                                                              \
+    constexpr int CT = kColThreads / lane_group(N);                                             \
+    dim3 grid(nf + (f.ncols_max + CT - 1) / CT, f.nb_max, f.nitems);                            \
+    hipLaunchKernelGGL(kb_col_inv_proj<N>, grid, dim3(kColThreads), 0, s, D, nf, sel_in, alpha, \
+                       coef_step);                                                              \
+    return hipGetLastError();                                                                   \
+  }
+  PW_FAST_SIZES(CASE)
+#undef CASE
+  return hipErrorInvalidValue;
 }
 hipError_t launch_fused_col_fwd_nl(const FusedFft& f, const ItemDev* D, int sel_in, int sel_out,
                                    int sel_prev, double alpha, double beta, double gamma,

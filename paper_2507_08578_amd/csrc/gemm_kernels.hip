@@ -394,92 +394,6 @@ __global__ void k_splitk_reduce_upper(int64_t M, int nsplit, int nact, const cpl
   C[i + j * ldc] = make_double2(alpha * re, alpha * im);
 }
 
-// ---- P^H psi for few projectors and plane waves (nonlocal_in_columns): one
-// workgroup forms kFewProj rows of one band's column of C, every thread a
-// slice of the plane waves, kFewUnroll of them loaded at once, so there are no
-// partials to reduce.  Bound by the latency of its loads: 8 x 16 outputs over
-// 1189 values 10.5 + 3.7 us as split product and reduction, 2.7 here.  Four rows
-// per workgroup: eight take 3.7 us, two the same as four but 23 instead of 21
-// us for 576 bands of 3001 values; the sums over lanes go through LDS (by
-// shuffles 3.0 us).
-constexpr int kFewProj = 4, kFewThreads = 256, kFewUnroll = 3;
-__device__ __forceinline__ void proj_few_body(int M, int K, const double* __restrict__ rowscale,
-                                              double alpha, const cplx* __restrict__ A, int64_t lda,
-                                              const cplx* __restrict__ x, cplx* __restrict__ C,
-                                              cplx* __restrict__ Craw, int j0) {
-  constexpr int W = kFewThreads / 64, V = 2 * kFewProj, L = 64 / V;   // L lanes add up a value
-  __shared__ double buf[W][V][65];
-  __shared__ double part[W][V];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nj = min(kFewProj, M - j0);
-  const double rs = rowscale && tid < nj ? rowscale[j0 + tid] : 1.0;
-  const cplx* a[kFewProj];
-#pragma unroll
-  for (int j = 0; j < kFewProj; ++j) a[j] = A + (j0 + min(j, nj - 1)) * lda;   // rows past M: not stored
-  double acc[V];
-#pragma unroll
-  for (int q = 0; q < V; ++q) acc[q] = 0.0;
-  for (int g0 = tid; g0 < K; g0 += kFewThreads * kFewUnroll) {
-    d2 v[kFewUnroll], p[kFewUnroll][kFewProj];
-#pragma unroll
-    for (int u = 0; u < kFewUnroll; ++u) {
-      const int g = min(g0 + u * kFewThreads, K - 1);
-      v[u] = ld2(x + g);
-#pragma unroll
-      for (int j = 0; j < kFewProj; ++j) p[u][j] = ld2(a[j] + g);
-    }
-#pragma unroll
-    for (int u = 0; u < kFewUnroll; ++u) {
-      if (u > 0 && g0 + u * kFewThreads >= K) break;
-#pragma unroll
-      for (int j = 0; j < kFewProj; ++j) {
-        acc[2 * j] += p[u][j].x * v[u].x + p[u][j].y * v[u].y;
-        acc[2 * j + 1] += p[u][j].x * v[u].y - p[u][j].y * v[u].x;
-      }
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < V; ++q) buf[wave][q][lane] = acc[q];
-  __syncthreads();
-  double s = 0.0;
-#pragma unroll
-  for (int i = 0; i < V; ++i) s += buf[wave][lane / L][(lane % L) * V + i];
-#pragma unroll
-  for (int t = L / 2; t > 0; t >>= 1) s += __shfl_xor(s, t, 64);
-  if (lane % L == 0) part[wave][lane / L] = s;
-  __syncthreads();
-  if (tid < nj) {
-    double re = 0.0, im = 0.0;
-#pragma unroll
-    for (int q = 0; q < W; ++q) {
-      re += part[q][2 * tid];
-      im += part[q][2 * tid + 1];
-    }
-    C[j0 + tid] = make_double2(alpha * rs * re, alpha * rs * im);
-    if (Craw) Craw[j0 + tid] = make_double2(alpha * re, alpha * im);
-  }
-}
-
-__global__ void __launch_bounds__(kFewThreads)
-k_proj_few(int64_t M, int64_t K, const double* __restrict__ rowscale, double alpha,
-           const double* __restrict__ alpha_dev, const cplx* __restrict__ A, int64_t lda,
-           const cplx* __restrict__ B, int64_t ldb, cplx* __restrict__ C, cplx* __restrict__ Craw) {
-  if (alpha_dev) alpha = alpha_dev[0];
-  const int64_t b = blockIdx.x;
-  proj_few_body((int)M, (int)K, rowscale, alpha, A, lda, B + b * ldb, C + b * M, Craw ? Craw + b * M : nullptr,
-                blockIdx.y * kFewProj);
-}
-
-__global__ void __launch_bounds__(kFewThreads)
-kb_proj_few(const ItemDev* __restrict__ D, int sel_b, double alpha, int coef_step) {
-  const ItemDev& d = D[blockIdx.z];
-  if ((int)blockIdx.x >= d.nb || (int)blockIdx.y * kFewProj >= d.nproj) return;
-  if (coef_step >= 0) alpha = d.coef[3 * coef_step];
-  const int64_t b = blockIdx.x;
-  proj_few_body(d.nproj, d.npw, d.ekb, alpha, d.proj, d.npw, item_blk64(d, sel_b) + b * d.npw,
-                d.cprj + b * d.nproj, nullptr, blockIdx.y * kFewProj);
-}
-
 struct SplitPlan {
   int64_t tiles_m, tiles_n, nsplit, ksplit;
 };
@@ -613,22 +527,6 @@ kb_gemm_nn(const ItemDev* __restrict__ D, int op, int sel_a, int sel_c) {
 size_t gemm_cn_work_elems(int64_t m, int64_t n, int64_t k) {
   const SplitPlan p = split_plan(m, n, k, kTargetBlocks);
   return p.nsplit > 1 ? (size_t)(p.nsplit * m * n) : 0;
-}
-
-hipError_t launch_proj_few(int64_t m, int64_t n, int64_t k, double alpha, const double* alpha_dev,
-                           const cplx* A, int64_t lda, const cplx* B, int64_t ldb, cplx* C,
-                           const double* rowscale, cplx* craw, hipStream_t s) {
-  if (m <= 0 || n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_proj_few, dim3((unsigned)n, (unsigned)((m + kFewProj - 1) / kFewProj)),
-                     dim3(kFewThreads), 0, s, m, k, rowscale, alpha, alpha_dev, A, lda, B, ldb, C, craw);
-  return hipGetLastError();
-}
-hipError_t launch_fused_proj_few(int nitems, int64_t m_max, int64_t n_max, const ItemDev* D, int sel_b,
-                                 double alpha, int coef_step, hipStream_t s) {
-  if (nitems <= 0 || m_max <= 0 || n_max <= 0) return hipSuccess;
-  const dim3 grid((unsigned)n_max, (unsigned)((m_max + kFewProj - 1) / kFewProj), nitems);
-  hipLaunchKernelGGL(kb_proj_few, grid, dim3(kFewThreads), 0, s, D, sel_b, alpha, coef_step);
-  return hipGetLastError();
 }
 
 int gemm_cn_fixed_target(int target) {

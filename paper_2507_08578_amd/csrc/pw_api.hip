@@ -167,8 +167,8 @@ pw_status ham_apply(pw_ham* h, int64_t nb, const cplx* in, int64_t ldin, cplx* o
   if (repro) cfg.pq64 = cfg.pq64_sq = false;
   const bool few = nonlocal_in_columns(h->nproj, h->npw, nb, cfg.reg_col);
   const int target = repro ? gemm_cn_fixed_target(h->gemm_target) : h->gemm_target;
-  const bool fork = h->nproj > 0 && c->overlap && c->stream == c->home;
-  if (h->nproj > 0) {
+  const bool fork = h->nproj > 0 && !few && c->overlap && c->stream == c->home;
+  if (h->nproj > 0 && !few) {
     // P^H psi on the second stream, concurrent with the FFT route below
     hipStream_t ps = fork ? c->aux : s;
     if (fork) {
@@ -176,13 +176,9 @@ pw_status ham_apply(pw_ham* h, int64_t nb, const cplx* in, int64_t ldin, cplx* o
       HIPCHK(c, hipStreamWaitEvent(ps, c->ev_fork, 0));
     }
     StageScope sc(c, PW_STAGE_PROJ, ps);
-    if (few)
-      HIPCHK(c, launch_proj_few(h->nproj, nb, h->npw, alpha, coef, h->proj, h->npw, in, ldin, h->cprj,
-                                h->ekb_dev, craw, ps));
-    else
-      HIPCHK(c, launch_gemm_cn(h->nproj, nb, h->npw, alpha, h->proj, h->npw, in, ldin, h->cprj,
-                               h->nproj, h->ekb_dev, h->gemm_work, ps, 0.0, coef, target, 0,
-                               craw, h->nproj));
+    HIPCHK(c, launch_gemm_cn(h->nproj, nb, h->npw, alpha, h->proj, h->npw, in, ldin, h->cprj,
+                             h->nproj, h->ekb_dev, h->gemm_work, ps, 0.0, coef, target, 0,
+                             craw, h->nproj));
   }
   if (fork) HIPCHK(c, hipEventRecord(c->ev_join, c->aux));
   const Epilogue ep{alpha, beta, gamma, coef};
@@ -190,14 +186,18 @@ pw_status ham_apply(pw_ham* h, int64_t nb, const cplx* in, int64_t ldin, cplx* o
     const int nc = (int)std::min<int64_t>(h->chunk, nb - c0);
     {
       StageScope sc(c, PW_STAGE_FFT_COL_INV);
-      HIPCHK(c, launch_fft_col_inv(h->plan, cfg, nc, in + c0 * ldin, ldin, h->T, s));
+      if (few)
+        HIPCHK(c, launch_fft_col_inv_proj(h->plan, nc, in + c0 * ldin, ldin, h->T, alpha, coef, h->proj,
+                                          h->nproj, h->npw, h->ekb_dev, h->cprj + c0 * h->nproj,
+                                          craw ? craw + c0 * h->nproj : nullptr, s));
+      else
+        HIPCHK(c, launch_fft_col_inv(h->plan, cfg, nc, in + c0 * ldin, ldin, h->T, s));
     }
     {
       StageScope sc(c, PW_STAGE_FFT_PLANE);
       HIPCHK(c, launch_fft_plane(h->plan, cfg, nc, h->vscaled, h->T, s));
     }
     {
-      if (few && fork && c0 == 0) HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));
       StageScope sc(c, PW_STAGE_FFT_COL_FWD);
       if (few)
         HIPCHK(c, launch_fft_col_fwd_nl(h->plan, nc, h->T, h->kin, in + c0 * ldin, ldin,
@@ -210,7 +210,7 @@ pw_status ham_apply(pw_ham* h, int64_t nb, const cplx* in, int64_t ldin, cplx* o
                                    ldout, ep, s));
     }
   }
-  if (fork && !few) HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));
+  if (fork) HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));
   if (h->nproj > 0 && !few) {
     StageScope sc(c, PW_STAGE_NONLOCAL);
     HIPCHK(c, launch_gemm_nn(h->npw, nb, h->nproj, 1.0, h->proj, h->npw, h->cprj, h->nproj, 1.0,
@@ -742,11 +742,9 @@ pw_status fused_apply(pw_ctx* c, const pw_batch::Group& g, int prec, int in, int
   const int bf16 = prec == PW_BF16;
   const int lps = lp ? PW_STAGE_FFT_COL_INV_LP - PW_STAGE_FFT_COL_INV : 0;
   const bool few = g.few && !lp;
-  if (g.nproj_max > 0) {
+  if (g.nproj_max > 0 && !few) {
     StageScope sc(c, PW_STAGE_PROJ + lps);
-    if (few)
-      HIPCHK(c, launch_fused_proj_few(g.nitems, g.nproj_max, g.nb_max, g.D, in, alpha, coef_step, s));
-    else if (lp)
+    if (lp)
       HIPCHK(c, launch_fused_gemm_cn32(bf16, g.nitems, g.nproj_max, g.nb_max, g.nsplit_proj32, g.D,
                                        in, alpha, coef_step, s));
     else
@@ -755,7 +753,10 @@ pw_status fused_apply(pw_ctx* c, const pw_batch::Group& g, int prec, int in, int
   }
   {
     StageScope sc(c, PW_STAGE_FFT_COL_INV + lps);
-    HIPCHK(c, launch_fused_col_inv(g.f, lp, g.D, in, s));
+    if (few)
+      HIPCHK(c, launch_fused_col_inv_proj(g.f, g.nproj_max, g.D, in, alpha, coef_step, s));
+    else
+      HIPCHK(c, launch_fused_col_inv(g.f, lp, g.D, in, s));
   }
   {
     StageScope sc(c, PW_STAGE_FFT_PLANE + lps);

@@ -415,22 +415,24 @@ __device__ __forceinline__ bool splitk_sum(const W* __restrict__ work, int64_t s
   return true;
 }
 
-// Few projectors: FP64 H*psi forms P^H psi without partials (launch_proj_few) and
-// adds P C while the column kernel emits its points (launch_fft_col_fwd_nl),
-// two launches less and no extra pass over the block: 8 atoms (8 projectors,
-// 1189 plane waves, 16 bands) 31.5 -> 17.3 us.  Each band reads P again, from L2,
-// so the line is where P fits beside the rest there (1 MiB) and the matrix
-// cores' tiles would hold few rows or columns.
+// Few projectors: FP64 H*psi forms P^H psi without partials, in the launch that
+// also transforms the columns (launch_fft_col_inv_proj), and adds P C while the
+// column kernel emits its points (launch_fft_col_fwd_nl): three launches in all
+// and no extra pass over the block: 8 atoms (8 projectors, 1189 plane waves, 16
+// bands) 31.5 -> 14.7 us; with the projections in a launch of their own 17.3.
+// Each band reads P again, from L2, so the line is where P fits beside the rest
+// there (1 MiB) and the matrix cores' tiles would hold few rows or columns.
 constexpr int64_t kNlMaxProj = 16, kNlMaxEntries = 65536;
 inline bool nonlocal_in_columns(int64_t nproj, int64_t npw, int64_t nb, bool reg_col) {
   return reg_col && nproj > 0 && nproj <= kNlMaxProj && nproj * npw <= kNlMaxEntries &&
          nb <= kReproBands;
 }
-hipError_t launch_proj_few(int64_t m, int64_t n, int64_t k, double alpha, const double* alpha_dev,
-                           const cplx* A, int64_t lda, const cplx* B, int64_t ldb, cplx* C,
-                           const double* rowscale, cplx* craw, hipStream_t s);
-hipError_t launch_fused_proj_few(int nitems, int64_t m_max, int64_t n_max, const ItemDev* D, int sel_b,
-                                 double alpha, int coef_step, hipStream_t s);
+hipError_t launch_fft_col_inv_proj(const BoxPlan& p, int nb, const cplx* psi, int64_t ldpsi, cplx* T,
+                                   double alpha, const double* alpha_dev, const cplx* proj,
+                                   int64_t nproj, int64_t npw, const double* rowscale, cplx* c,
+                                   cplx* craw, hipStream_t s);
+hipError_t launch_fused_col_inv_proj(const FusedFft& f, int64_t nproj_max, const ItemDev* D,
+                                     int sel_in, double alpha, int coef_step, hipStream_t s);
 hipError_t launch_fft_col_fwd_nl(const BoxPlan& p, int nb, const cplx* T, const double* kin,
                                  const cplx* in, int64_t ldin, const cplx* prev, int64_t ldprev,
                                  cplx* out, int64_t ldout, const Epilogue& ep, const cplx* proj,
