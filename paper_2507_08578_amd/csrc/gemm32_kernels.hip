@@ -10,15 +10,14 @@
 //              and P C (gemm_nn32_s3) read P's terms from copies made once
 //              per handle; P^H psi splits psi per stage, and the reduction
 //              that forms C stores C's terms.  Gram matrices Y^H Y
-//              (gemm_cn32) split both operands per stage.  Without the copies
-//              P C runs on v_mfma_f32_16x16x4f32 with FP32 operands.
+//              (gemm_cn32) split both operands per stage.
 //   MODE_BF16: v_mfma_f32_16x16x32_bf16, operands rounded to bfloat16
-//              (round to nearest even) when the MFMA operands are formed from
-//              the FP32 tiles staged in LDS.
+//              (round to nearest even).  P^H psi (gemm_cn32_h1) and P C
+//              (gemm_nn32_h1) read the first terms of the same copies; Gram
+//              matrices (gemm_cn32) round their FP32 tiles staged in LDS.
 // Operand layouts (checked on the device):
-//   f32 16x16x4 : A lane l -> A[l%16][l/16], B lane l -> B[l/16][l%16]
 //   bf16 16x16x32: A lane l -> A[l%16][8(l/16)+e], B lane l -> B[8(l/16)+e][l%16], e < 8
-//   result (both): lane l, element r -> D[4(l/16) + r][l%16]
+//   result: lane l, element r -> D[4(l/16) + r][l%16]
 // A complex product is four real MFMAs into two accumulators:
 //   re += ar br - ai bi,  im += ar bi + ai br.
 #include "pw_internal.h"
@@ -41,158 +40,41 @@ struct KC {
 
 __device__ __forceinline__ void f4zero(f4& a) { a = f4{0.f, 0.f, 0.f, 0.f}; }
 
-// One complex K-stage of MFMAs for a wave's TM x TN sub-tiles.  As/Bs are LDS
-// tiles [k][i] / [k][j] (row pitch pa/pb in float2); conjA negates Im(A).
-template <int MODE, bool CONJA, int TM = 2, int TN = 2>
+// One complex K-stage of bf16 MFMAs conj(A) B for a wave's 2 x 2 sub-tiles.
+// As/Bs are LDS tiles [k][i] / [k][j] (row pitch pa/pb in float2).
 __device__ __forceinline__ void mfma_stage(const float2* As, int pa, const float2* Bs, int pb,
-                                           int wi, int wj, int lane, f4 (&ar)[TM][TN],
-                                           f4 (&ai)[TM][TN]) {
+                                           int wi, int wj, int lane, f4 (&ar)[2][2],
+                                           f4 (&ai)[2][2]) {
   const int lr = lane & 15, lk = lane >> 4;
-  if constexpr (MODE == MODE_F32) {
+  bf8 are[2], aim[2], anim[2], bre[2], bim[2];
 #pragma unroll
-    for (int ks = 0; ks < KC<MODE>::value; ks += 4) {
-      float2 a[TM], b[TN];
+  for (int t = 0; t < 2; ++t) {
 #pragma unroll
-      for (int t = 0; t < TM; ++t) {
-        a[t] = As[(ks + lk) * pa + wi * 16 * TM + t * 16 + lr];
-        if (CONJA) a[t].y = -a[t].y;
-      }
-#pragma unroll
-      for (int t = 0; t < TN; ++t) b[t] = Bs[(ks + lk) * pb + wj * 16 * TN + t * 16 + lr];
-#pragma unroll
-      for (int ti = 0; ti < TM; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < TN; ++tj) {
-          ar[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ti].x, b[tj].x, ar[ti][tj], 0, 0, 0);
-          ar[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(-a[ti].y, b[tj].y, ar[ti][tj], 0, 0, 0);
-          ai[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ti].x, b[tj].y, ai[ti][tj], 0, 0, 0);
-          ai[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ti].y, b[tj].x, ai[ti][tj], 0, 0, 0);
-        }
+    for (int e = 0; e < 8; ++e) {
+      const float2 a = As[(8 * lk + e) * pa + wi * 32 + t * 16 + lr];
+      are[t][e] = (__bf16)a.x;
+      aim[t][e] = (__bf16)(-a.y);
+      anim[t][e] = (__bf16)a.y;
     }
-  } else {
-    bf8 are[TM], aim[TM], anim[TM], bre[TN], bim[TN];
-#pragma unroll
-    for (int t = 0; t < TM; ++t) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        float2 a = As[(8 * lk + e) * pa + wi * 16 * TM + t * 16 + lr];
-        if (CONJA) a.y = -a.y;
-        are[t][e] = (__bf16)a.x;
-        aim[t][e] = (__bf16)a.y;
-        anim[t][e] = (__bf16)(-a.y);
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < TN; ++t) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float2 b = Bs[(8 * lk + e) * pb + wj * 16 * TN + t * 16 + lr];
-        bre[t][e] = (__bf16)b.x;
-        bim[t][e] = (__bf16)b.y;
-      }
-    }
-#pragma unroll
-    for (int ti = 0; ti < TM; ++ti)
-#pragma unroll
-      for (int tj = 0; tj < TN; ++tj) {
-        ar[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(are[ti], bre[tj], ar[ti][tj], 0, 0, 0);
-        ar[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(anim[ti], bim[tj], ar[ti][tj], 0, 0, 0);
-        ai[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(are[ti], bim[tj], ai[ti][tj], 0, 0, 0);
-        ai[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aim[ti], bre[tj], ai[ti][tj], 0, 0, 0);
-      }
   }
-}
-
-// C = alpha A B + beta C; A m x k (lda), B k x n (ldb), complex64 column-major.
-// Workgroup tile (32 TM) x (32 TN), 4 waves in 2 x 2.
-template <int MODE, int TM, int TN, class SC = float2>
-__device__ __forceinline__ void gemm_nn32_tile(int64_t M, int64_t N, int64_t K, float alpha,
-                                               const float2* __restrict__ A, int64_t lda,
-                                               const float2* __restrict__ B, int64_t ldb,
-                                               float beta, SC* __restrict__ C, int64_t ldc,
-                                               int bx, int by) {
-  constexpr int Kc = KC<MODE>::value;
-  constexpr int BM = 32 * TM, BN = 32 * TN;
-  constexpr int PA = BM, PB = BN + 1;
-  __shared__ float2 As[Kc * PA];
-  __shared__ float2 Bs[Kc * PB];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wi = wave >> 1, wj = wave & 1;
-  const int64_t i0 = (int64_t)by * BM, j0 = (int64_t)bx * BN;
-  f4 ar[TM][TN], ai[TM][TN];
 #pragma unroll
-  for (int a = 0; a < TM; ++a)
+  for (int t = 0; t < 2; ++t) {
 #pragma unroll
-    for (int b = 0; b < TN; ++b) {
-      f4zero(ar[a][b]);
-      f4zero(ai[a][b]);
+    for (int e = 0; e < 8; ++e) {
+      const float2 b = Bs[(8 * lk + e) * pb + wj * 32 + t * 16 + lr];
+      bre[t][e] = (__bf16)b.x;
+      bim[t][e] = (__bf16)b.y;
     }
-  constexpr int QA = BM * Kc / kThreads, QB = BN * Kc / kThreads;
-  static_assert(QA * kThreads == BM * Kc && QB * kThreads == BN * Kc, "tile split");
-  float2 ra[QA], rb[QB];
-  auto fetch = [&](int64_t k0) {
-#pragma unroll
-    for (int q = 0; q < QA; ++q) {
-      const int e = tid + q * kThreads;
-      const int kk = e / BM, ii = e - kk * BM;
-      const int64_t gi = i0 + ii, gk = k0 + kk;
-      ra[q] = (gi < M && gk < K) ? A[gi + gk * lda] : make_float2(0.f, 0.f);
-    }
-#pragma unroll
-    for (int q = 0; q < QB; ++q) {
-      const int e = tid + q * kThreads;
-      const int jj = e / Kc, kk = e - jj * Kc;
-      const int64_t gk = k0 + kk, gj = j0 + jj;
-      rb[q] = (gk < K && gj < N) ? B[gk + gj * ldb] : make_float2(0.f, 0.f);
-    }
-  };
-  fetch(0);
-  for (int64_t k0 = 0; k0 < K; k0 += Kc) {
-#pragma unroll
-    for (int q = 0; q < QA; ++q) {
-      const int e = tid + q * kThreads;
-      const int kk = e / BM, ii = e - kk * BM;
-      As[kk * PA + ii] = ra[q];
-    }
-#pragma unroll
-    for (int q = 0; q < QB; ++q) {
-      const int e = tid + q * kThreads;
-      const int jj = e / Kc, kk = e - jj * Kc;
-      Bs[kk * PB + jj] = rb[q];
-    }
-    __syncthreads();
-    if (k0 + Kc < K) fetch(k0 + Kc);
-    mfma_stage<MODE, false, TM, TN>(As, PA, Bs, PB, wi, wj, lane, ar, ai);
-    __syncthreads();
   }
-  const int lr = lane & 15, lk = lane >> 4;
 #pragma unroll
-  for (int ti = 0; ti < TM; ++ti)
+  for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
-    for (int tj = 0; tj < TN; ++tj)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t i = i0 + wi * 16 * TM + ti * 16 + 4 * lk + r;
-        const int64_t j = j0 + wj * 16 * TN + tj * 16 + lr;
-        if (i < M && j < N) {
-          float2 v = make_float2(alpha * ar[ti][tj][r], alpha * ai[ti][tj][r]);
-          if (beta != 0.f) {
-            const float2 c = ld_c(C[i + j * ldc]);
-            v.x += beta * c.x;
-            v.y += beta * c.y;
-          }
-          C[i + j * ldc] = st_c<SC>(v);
-        }
-      }
-}
-
-template <int MODE>
-__device__ __forceinline__ void gemm_nn32_body(int64_t M, int64_t N, int64_t K, float alpha,
-                                               const float2* __restrict__ A, int64_t lda,
-                                               const float2* __restrict__ B, int64_t ldb,
-                                               float beta, float2* __restrict__ C, int64_t ldc,
-                                               int bx, int by) {
-  gemm_nn32_tile<MODE, 2, 2>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, bx, by);
+    for (int tj = 0; tj < 2; ++tj) {
+      ar[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(are[ti], bre[tj], ar[ti][tj], 0, 0, 0);
+      ar[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(anim[ti], bim[tj], ar[ti][tj], 0, 0, 0);
+      ai[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(are[ti], bim[tj], ai[ti][tj], 0, 0, 0);
+      ai[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aim[ti], bre[tj], ai[ti][tj], 0, 0, 0);
+    }
 }
 
 // Workgroups are dealt round-robin over the device's XCDs (each with its own
@@ -210,26 +92,6 @@ __device__ __forceinline__ bool xcd_panel_tile(int L, int tiles_m, int tiles_n, 
   *by = panel;
   *bx = slot % tiles_n;
   return true;
-}
-
-template <int MODE, class SC = float2>
-__global__ void __launch_bounds__(kThreads)
-k_gemm_nn32(int64_t M, int64_t N, int64_t K, float alpha, const float2* __restrict__ A,
-            int64_t lda, const float2* __restrict__ B, int64_t ldb, float beta,
-            SC* __restrict__ C, int64_t ldc, int tiles_m, int tiles_n) {
-  int bx, by;
-  if (!xcd_panel_tile(blockIdx.x, tiles_m, tiles_n, &bx, &by)) return;
-  gemm_nn32_tile<MODE, 2, 2, SC>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, bx, by);
-}
-
-template <int MODE, class SC = float2>
-__global__ void __launch_bounds__(kThreads)
-k_gemm_nn32_tall(int64_t M, int64_t N, int64_t K, float alpha, const float2* __restrict__ A,
-                 int64_t lda, const float2* __restrict__ B, int64_t ldb, float beta,
-                 SC* __restrict__ C, int64_t ldc, int tiles_m, int tiles_n) {
-  int bx, by;
-  if (!xcd_panel_tile(blockIdx.x, tiles_m, tiles_n, &bx, &by)) return;
-  gemm_nn32_tile<MODE, 4, 2, SC>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, bx, by);
 }
 
 // ---- P^H psi with FP32 operands on the bf16 matrix cores.
@@ -516,13 +378,12 @@ __device__ __forceinline__ void gemm_cn32_s3_body(int64_t M, int64_t N, int64_t 
 }
 
 // Partial (split z over K) A^H B; A k x m (lda), B k x n (ldb); out ld = M.
-template <int MODE, class SB = float2>
+template <int MODE>
 __device__ __forceinline__ void gemm_cn32_body(int64_t M, int64_t N, int64_t K, int64_t ksplit,
                                                const float2* __restrict__ A, int64_t lda,
-                                               const SB* __restrict__ B, int64_t ldb,
+                                               const float2* __restrict__ B, int64_t ldb,
                                                float2* __restrict__ out, int bx, int by, int bz) {
   if constexpr (MODE == MODE_F32) {
-    static_assert(sizeof(SB) == sizeof(float2), "FP32 operands only");
     gemm_cn32_b3_body(M, N, K, ksplit, A, lda, B, ldb, out, bx, by, bz);
     return;
   }
@@ -559,7 +420,7 @@ __device__ __forceinline__ void gemm_cn32_body(int64_t M, int64_t N, int64_t K, 
       const int e = tid + q * kThreads;
       const int jj = e / Kc, kk = e - jj * Kc;
       const int64_t gj = j0 + jj, gk = k0 + kk;
-      rb[q] = (gj < N && gk < ke) ? ld_c(B[gk + gj * ldb]) : make_float2(0.f, 0.f);
+      rb[q] = (gj < N && gk < ke) ? B[gk + gj * ldb] : make_float2(0.f, 0.f);
     }
   };
   if (kb < ke) fetch(kb);
@@ -578,7 +439,7 @@ __device__ __forceinline__ void gemm_cn32_body(int64_t M, int64_t N, int64_t K, 
     }
     __syncthreads();
     if (k0 + Kc < ke) fetch(k0 + Kc);
-    mfma_stage<MODE, true>(As, PA, Bs, PB, wi, wj, lane, ar, ai);
+    mfma_stage(As, PA, Bs, PB, wi, wj, lane, ar, ai);
     __syncthreads();
   }
   float2* o = out + (int64_t)bz * M * N;
@@ -687,6 +548,240 @@ k_gemm_nn32_s3(int64_t M, int64_t N, int64_t K, float alpha, const __bf16* __res
   gemm_nn32_s3_body(M, N, K, alpha, A3, B3, beta, C, ldc, bx, by);
 }
 
+// ---- Products with bf16 operands, from the stored copies: a value rounded to
+// bf16 is the first of its three terms, so planes 0 and 1 of a chunk (its first
+// 128 bytes) are the operand.  The complex64 projectors are twice those bytes,
+// had to be rounded by every column tile and went through LDS as FP32: 64 atoms
+// (256 projectors, 37073 plane waves, 160 bands) P^H psi 110 us and P C 80, here
+// 35 and 48 (85 MB, P read and the block read and written: 18 us at copy speed).
+constexpr int kH1Chunks = 2;   // 32-K chunks per LDS stage
+
+// Planes 0 and 1 of 32-K chunk u of a stage in LDS: R rows each
+template <int R>
+__device__ __forceinline__ bf8* h1_at(__bf16* L, int u, int c, int row, int k8) {
+  return reinterpret_cast<bf8*>(L + ((u * 2 + c) * R + row) * kB3Pitch + k8);
+}
+
+// One 32-K step of a (16 TM) x 32 wavefront tile: a and b the LDS rows of the
+// wavefront's first row and column; conj(A) with CONJA.
+template <bool CONJA, int TM, int RA>
+__device__ __forceinline__ void h1_step(__bf16* LA, __bf16* LB, int u, int r0, int c0, int lr, int lk,
+                                        f4 (&ar)[TM][2], f4 (&ai)[TM][2]) {
+  typedef unsigned u4 __attribute__((ext_vector_type(4)));
+  bf8 are[TM], aim[TM], anim[TM], bre[2], bim[2];
+#pragma unroll
+  for (int t = 0; t < TM; ++t) {
+    are[t] = *h1_at<RA>(LA, u, 0, r0 + t * 16 + lr, 8 * lk);
+    const bf8 y = *h1_at<RA>(LA, u, 1, r0 + t * 16 + lr, 8 * lk);
+    const bf8 ny = __builtin_bit_cast(bf8, __builtin_bit_cast(u4, y) ^ 0x80008000u);
+    aim[t] = CONJA ? ny : y;
+    anim[t] = CONJA ? y : ny;
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    bre[t] = *h1_at<64>(LB, u, 0, c0 + t * 16 + lr, 8 * lk);
+    bim[t] = *h1_at<64>(LB, u, 1, c0 + t * 16 + lr, 8 * lk);
+  }
+#pragma unroll
+  for (int ti = 0; ti < TM; ++ti)
+#pragma unroll
+    for (int tj = 0; tj < 2; ++tj) {
+      ar[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(are[ti], bre[tj], ar[ti][tj], 0, 0, 0);
+      ar[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(anim[ti], bim[tj], ar[ti][tj], 0, 0, 0);
+      ai[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(are[ti], bim[tj], ai[ti][tj], 0, 0, 0);
+      ai[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aim[ti], bre[tj], ai[ti][tj], 0, 0, 0);
+    }
+}
+
+__device__ __forceinline__ void h1_pack(const bf16c (&x)[8], bf8& re, bf8& im) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    re[e] = __builtin_bit_cast(__bf16, x[e].re);
+    im[e] = __builtin_bit_cast(__bf16, x[e].im);
+  }
+}
+__device__ __forceinline__ void h1_pack(const float2 (&x)[8], bf8& re, bf8& im) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    re[e] = (__bf16)x[e].x;
+    im[e] = (__bf16)x[e].y;
+  }
+}
+
+// Partial (split z over K) A^H B, A3 and B as in gemm_cn32_s3_body, B complex64
+// (rounded as it is staged) or bf16 pairs.  Chunks past ke are neither read nor
+// multiplied.
+template <class SB>
+__device__ __forceinline__ void gemm_cn32_h1_body(int64_t M, int64_t N, int64_t K, int64_t ksplit,
+                                                  const __bf16* __restrict__ A3,
+                                                  const SB* __restrict__ B, int64_t ldb,
+                                                  float2* __restrict__ out, int bx, int by, int bz) {
+  __shared__ __align__(16) __bf16 LA[2 * kH1Chunks * kB3Plane];
+  __shared__ __align__(16) __bf16 LB[2 * kH1Chunks * kB3Plane];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wi = wave >> 1, wj = wave & 1;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int row = tid >> 2, k8 = (tid & 3) * 8;
+  const int64_t i0 = (int64_t)by * kBM, j0 = (int64_t)bx * kBN;
+  const int64_t kb = (int64_t)bz * ksplit;
+  const int64_t ke = min(K, kb + ksplit);
+  f4 ar[2][2], ai[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      f4zero(ar[a][b]);
+      f4zero(ai[a][b]);
+    }
+  const __bf16* pa = A3 + ((i0 + row) * s3_nst(K) + (kb >> 5)) * kS3Chunk + k8;
+  const SB* pb = B + min(j0 + row, N - 1) * ldb + kb + k8;
+  bf8 ra[kH1Chunks][2];
+  SB xb[kH1Chunks][8];
+  auto fetch = [&](int64_t k0) {
+#pragma unroll
+    for (int u = 0; u < kH1Chunks; ++u) {
+      const int64_t k = k0 + u * kB3K;
+      if (k >= ke) break;
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        ra[u][c] = *reinterpret_cast<const bf8*>(pa + u * kS3Chunk + c * 32);
+      if (k + kB3K <= ke) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) xb[u][e] = pb[u * kB3K + e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) xb[u][e] = k + k8 + e < ke ? pb[u * kB3K + e] : SB{};
+      }
+    }
+    pa += kH1Chunks * kS3Chunk;
+    pb += kH1Chunks * kB3K;
+  };
+  if (kb < ke) fetch(kb);
+  for (int64_t k0 = kb; k0 < ke; k0 += kH1Chunks * kB3K) {
+#pragma unroll
+    for (int u = 0; u < kH1Chunks; ++u) {
+      if (k0 + u * kB3K >= ke) break;
+      bf8 re, im;
+      h1_pack(xb[u], re, im);
+      *h1_at<64>(LA, u, 0, row, k8) = ra[u][0];
+      *h1_at<64>(LA, u, 1, row, k8) = ra[u][1];
+      *h1_at<64>(LB, u, 0, row, k8) = re;
+      *h1_at<64>(LB, u, 1, row, k8) = im;
+    }
+    __syncthreads();
+    const int64_t k1 = k0 + kH1Chunks * kB3K;
+    if (k1 < ke) fetch(k1);
+#pragma unroll
+    for (int u = 0; u < kH1Chunks; ++u)
+      if (k0 + u * kB3K < ke) h1_step<true, 2, 64>(LA, LB, u, wi * 32, wj * 32, lr, lk, ar, ai);
+    __syncthreads();
+  }
+  float2* o = out + (int64_t)bz * M * N;
+#pragma unroll
+  for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+    for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t i = i0 + wi * 32 + ti * 16 + 4 * lk + r;
+        const int64_t j = j0 + wj * 32 + tj * 16 + lr;
+        if (i < M && j < N) o[i + j * M] = make_float2(ar[ti][tj][r], ai[ti][tj][r]);
+      }
+}
+
+// out = alpha P C + beta out on a (32 TM) x 64 tile, A3 and B3 as in
+// gemm_nn32_s3_body.  A3 has rows to the next multiple of 64: a tile of 128
+// reads the last of them for those past it (not stored).
+template <int TM, class SC>
+__device__ __forceinline__ void gemm_nn32_h1_body(int64_t M, int64_t N, int64_t K, float alpha,
+                                                  const __bf16* __restrict__ A3,
+                                                  const __bf16* __restrict__ B3, float beta,
+                                                  SC* __restrict__ C, int64_t ldc, int bx, int by) {
+  constexpr int BM = 32 * TM, H = BM / 64;
+  __shared__ __align__(16) __bf16 LA[2 * kH1Chunks * BM * kB3Pitch];
+  __shared__ __align__(16) __bf16 LB[2 * kH1Chunks * kB3Plane];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wi = wave >> 1, wj = wave & 1;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int row = tid >> 2, k8 = (tid & 3) * 8;
+  const int64_t i0 = (int64_t)by * BM, j0 = (int64_t)bx * kBN;
+  const int64_t nst = s3_nst(K);
+  f4 ar[TM][2], ai[TM][2];
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      f4zero(ar[a][b]);
+      f4zero(ai[a][b]);
+    }
+  const __bf16* pa[H];
+#pragma unroll
+  for (int h = 0; h < H; ++h)
+    pa[h] = A3 + min(i0 + row + h * 64, s3_rows(M) - 1) * nst * kS3Chunk + k8;
+  const __bf16* pb = B3 + (j0 + row) * nst * kS3Chunk + k8;
+  bf8 ra[kH1Chunks][H][2], rb[kH1Chunks][2];
+  auto fetch = [&](int64_t st) {
+#pragma unroll
+    for (int u = 0; u < kH1Chunks; ++u) {
+      if (st + u >= nst) break;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int64_t at = (st + u) * kS3Chunk + c * 32;
+#pragma unroll
+        for (int h = 0; h < H; ++h) ra[u][h][c] = *reinterpret_cast<const bf8*>(pa[h] + at);
+        rb[u][c] = *reinterpret_cast<const bf8*>(pb + at);
+      }
+    }
+  };
+  fetch(0);
+  for (int64_t st = 0; st < nst; st += kH1Chunks) {
+#pragma unroll
+    for (int u = 0; u < kH1Chunks; ++u) {
+      if (st + u >= nst) break;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+#pragma unroll
+        for (int h = 0; h < H; ++h) *h1_at<BM>(LA, u, c, row + h * 64, k8) = ra[u][h][c];
+        *h1_at<64>(LB, u, c, row, k8) = rb[u][c];
+      }
+    }
+    __syncthreads();
+    if (st + kH1Chunks < nst) fetch(st + kH1Chunks);
+#pragma unroll
+    for (int u = 0; u < kH1Chunks; ++u)
+      if (st + u < nst) h1_step<false, TM, BM>(LA, LB, u, wi * 16 * TM, wj * 32, lr, lk, ar, ai);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int ti = 0; ti < TM; ++ti)
+#pragma unroll
+    for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t i = i0 + wi * 16 * TM + ti * 16 + 4 * lk + r;
+        const int64_t j = j0 + wj * 32 + tj * 16 + lr;
+        if (i < M && j < N) {
+          float2 v = make_float2(alpha * ar[ti][tj][r], alpha * ai[ti][tj][r]);
+          if (beta != 0.f) {
+            const float2 c = ld_c(C[i + j * ldc]);
+            v.x += beta * c.x;
+            v.y += beta * c.y;
+          }
+          C[i + j * ldc] = st_c<SC>(v);
+        }
+      }
+}
+
+template <int TM, class SC>
+__global__ void __launch_bounds__(kThreads)
+k_gemm_nn32_h1(int64_t M, int64_t N, int64_t K, float alpha, const __bf16* __restrict__ A3,
+               const __bf16* __restrict__ B3, float beta, SC* __restrict__ C, int64_t ldc,
+               int tiles_m, int tiles_n) {
+  int bx, by;
+  if (!xcd_panel_tile(blockIdx.x, tiles_m, tiles_n, &bx, &by)) return;
+  gemm_nn32_h1_body<TM, SC>(M, N, K, alpha, A3, B3, beta, C, ldc, bx, by);
+}
+
 // The stored three-term copy X3 of a complex64 matrix X (R rows, contraction
 // K; element (r, k) at X[r sr + k sk]), all s3_rows(R) x 32 nst entries
 // written (zero padding included).  A workgroup per 64-row panel and K chunk
@@ -741,14 +836,14 @@ __device__ __forceinline__ bool xcd_split_tile(int L, int tiles_m, int tiles_n, 
   return true;
 }
 
-template <int MODE, class SB = float2>
+template <int MODE>
 __global__ void __launch_bounds__(kThreads)
 k_gemm_cn32(int64_t M, int64_t N, int64_t K, int64_t ksplit, const float2* __restrict__ A,
-            int64_t lda, const SB* __restrict__ B, int64_t ldb, float2* __restrict__ out,
+            int64_t lda, const float2* __restrict__ B, int64_t ldb, float2* __restrict__ out,
             int tiles_m, int tiles_n, int nsplit) {
   int bx, by, bz;
   if (!xcd_split_tile(blockIdx.x, tiles_m, tiles_n, nsplit, &bx, &by, &bz)) return;
-  gemm_cn32_body<MODE, SB>(M, N, K, ksplit, A, lda, B, ldb, out, bx, by, bz);
+  gemm_cn32_body<MODE>(M, N, K, ksplit, A, lda, B, ldb, out, bx, by, bz);
 }
 
 __global__ void __launch_bounds__(kThreads)
@@ -758,6 +853,16 @@ k_gemm_cn32_s3(int64_t M, int64_t N, int64_t K, int64_t ksplit, const __bf16* __
   int bx, by, bz;
   if (!xcd_split_tile(blockIdx.x, tiles_m, tiles_n, nsplit, &bx, &by, &bz)) return;
   gemm_cn32_s3_body(M, N, K, ksplit, A3, B, ldb, out, bx, by, bz);
+}
+
+template <class SB>
+__global__ void __launch_bounds__(kThreads)
+k_gemm_cn32_h1(int64_t M, int64_t N, int64_t K, int64_t ksplit, const __bf16* __restrict__ A3,
+               const SB* __restrict__ B, int64_t ldb, float2* __restrict__ out, int tiles_m,
+               int tiles_n, int nsplit) {
+  int bx, by, bz;
+  if (!xcd_split_tile(blockIdx.x, tiles_m, tiles_n, nsplit, &bx, &by, &bz)) return;
+  gemm_cn32_h1_body<SB>(M, N, K, ksplit, A3, B, ldb, out, bx, by, bz);
 }
 
 // C[i + j ldc] = alpha rowscale[i] sum_z work[z][i + j M] (FP64 sum, fixed order), rounded;
@@ -848,8 +953,9 @@ kb_gemm_cn32(const ItemDev* __restrict__ D, int sel_b, int nsplit_max) {
     gemm_cn32_s3_body(d.nproj, d.nb, d.npw, p.ksplit, reinterpret_cast<const __bf16*>(d.proj3c),
                       item_blk32(d, sel_b), d.npw, d.work32, blockIdx.x, blockIdx.y, zs);
   else
-    gemm_cn32_body<MODE>(d.nproj, d.nb, d.npw, p.ksplit, d.proj32, d.npw, item_blk32(d, sel_b),
-                         d.npw, d.work32, blockIdx.x, blockIdx.y, zs);
+    gemm_cn32_h1_body<float2>(d.nproj, d.nb, d.npw, p.ksplit,
+                              reinterpret_cast<const __bf16*>(d.proj3c), item_blk32(d, sel_b), d.npw,
+                              d.work32, blockIdx.x, blockIdx.y, zs);
 }
 
 template <int MODE>
@@ -859,8 +965,7 @@ __global__ void kb_splitk_reduce32(const ItemDev* __restrict__ D, double alpha, 
   const SplitPlan p = split_plan32<MODE>(d.nproj, d.nb, d.npw, d.gemm_target);
   const double* alpha_dev = coef_step >= 0 ? d.coef + 3 * coef_step : nullptr;
   splitk_reduce32_body(d.nproj, d.nb, (int)p.nsplit, d.work32, alpha, alpha_dev, d.ekb, d.cprj32,
-                       d.nproj, MODE == MODE_F32 ? reinterpret_cast<__bf16*>(d.cprj3) : nullptr,
-                       blockIdx.x);
+                       d.nproj, reinterpret_cast<__bf16*>(d.cprj3), blockIdx.x);
 }
 
 template <int MODE>
@@ -873,8 +978,9 @@ kb_gemm_nn32(const ItemDev* __restrict__ D, int sel_c) {
                       reinterpret_cast<const __bf16*>(d.cprj3), 1.f, item_blk32(d, sel_c), d.npw,
                       blockIdx.x, blockIdx.y);
   else
-    gemm_nn32_body<MODE>(d.npw, d.nb, d.nproj, 1.f, d.proj32, d.npw, d.cprj32, d.nproj, 1.f,
-                         item_blk32(d, sel_c), d.npw, blockIdx.x, blockIdx.y);
+    gemm_nn32_h1_body<2, float2>(d.npw, d.nb, d.nproj, 1.f, reinterpret_cast<const __bf16*>(d.proj3),
+                                 reinterpret_cast<const __bf16*>(d.cprj3), 1.f, item_blk32(d, sel_c),
+                                 d.npw, blockIdx.x, blockIdx.y);
 }
 
 }  // namespace
@@ -929,77 +1035,76 @@ hipError_t launch_gemm_cn32_s3(int64_t m, int64_t n, int64_t k, double alpha, co
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_cn32_s16(int64_t m, int64_t n, int64_t k, double alpha, const float2* A,
-                                int64_t lda, const bf16c* B, int64_t ldb, float2* C, int64_t ldc,
-                                const double* rowscale, float2* work, hipStream_t s,
-                                const double* alpha_dev, int target) {
+namespace {
+template <class SB>
+hipError_t gemm_cn32_h1(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3, const SB* B,
+                        int64_t ldb, float2* C, int64_t ldc, const double* rowscale, float2* work,
+                        hipStream_t s, const double* alpha_dev, int target, uint16_t* c3) {
   if (m <= 0 || n <= 0) return hipSuccess;
   const SplitPlan p = split_plan32<MODE_BF16>(m, n, k, target);
   const dim3 grid((unsigned)(kXcds * p.tiles_m * p.tiles_n * ((p.nsplit + kXcds - 1) / kXcds)));
-  hipLaunchKernelGGL((k_gemm_cn32<MODE_BF16, bf16c>), grid, dim3(kThreads), 0, s, m, n, k,
-                     p.ksplit, A, lda, B, ldb, work, (int)p.tiles_m, (int)p.tiles_n,
-                     (int)p.nsplit);
+  hipLaunchKernelGGL(k_gemm_cn32_h1<SB>, grid, dim3(kThreads), 0, s, m, n, k, p.ksplit,
+                     reinterpret_cast<const __bf16*>(a3), B, ldb, work, (int)p.tiles_m,
+                     (int)p.tiles_n, (int)p.nsplit);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t tot = m * n;
   hipLaunchKernelGGL(k_splitk_reduce32, dim3(splitk_blocks(tot, splitk_parts((int)p.nsplit))), dim3(256), 0, s, m, n,
                      (int)p.nsplit, (const float2*)work, alpha, alpha_dev, rowscale, C, ldc,
-                     (__bf16*)nullptr);
+                     reinterpret_cast<__bf16*>(c3));
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_nn32_s16(int64_t m, int64_t n, int64_t k, double alpha, const float2* A,
-                                int64_t lda, const float2* B, int64_t ldb, double beta, bf16c* C,
-                                int64_t ldc, hipStream_t s, int tile) {
+template <class SC>
+hipError_t gemm_nn32_h1(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3,
+                        const uint16_t* b3, double beta, SC* C, int64_t ldc, hipStream_t s, int tile) {
   if (m <= 0 || n <= 0) return hipSuccess;
-  const int tn = (int)((n + kBN - 1) / kBN);
-  if (tile == 1) {
-    const int tm = (int)((m + 2 * kBM - 1) / (2 * kBM));
-    const dim3 grid((unsigned)(kXcds * tn * ((tm + kXcds - 1) / kXcds)));
-    hipLaunchKernelGGL((k_gemm_nn32_tall<MODE_BF16, bf16c>), grid, dim3(kThreads), 0, s, m, n, k,
-                       (float)alpha, A, lda, B, ldb, (float)beta, C, ldc, tm, tn);
-    return hipGetLastError();
-  }
-  const int tm = (int)((m + kBM - 1) / kBM);
+  const int bm = tile == 1 ? 2 * kBM : kBM;
+  const int tn = (int)((n + kBN - 1) / kBN), tm = (int)((m + bm - 1) / bm);
   const dim3 grid((unsigned)(kXcds * tn * ((tm + kXcds - 1) / kXcds)));
-  hipLaunchKernelGGL((k_gemm_nn32<MODE_BF16, bf16c>), grid, dim3(kThreads), 0, s, m, n, k,
-                     (float)alpha, A, lda, B, ldb, (float)beta, C, ldc, tm, tn);
-  return hipGetLastError();
-}
-
-hipError_t launch_gemm_nn32(int bf16, int64_t m, int64_t n, int64_t k, double alpha, const float2* A,
-                            int64_t lda, const float2* B, int64_t ldb, double beta, float2* C,
-                            int64_t ldc, hipStream_t s, int tile, const uint16_t* a3,
-                            const uint16_t* b3) {
-  if (m <= 0 || n <= 0) return hipSuccess;
-  const int tn = (int)((n + kBN - 1) / kBN);
-  if (!bf16 && a3 && b3) {
-    const int tm = (int)((m + kBM - 1) / kBM);
-    const dim3 grid((unsigned)(kXcds * tn * ((tm + kXcds - 1) / kXcds)));
-    hipLaunchKernelGGL(k_gemm_nn32_s3, grid, dim3(kThreads), 0, s, m, n, k, (float)alpha,
-                       reinterpret_cast<const __bf16*>(a3), reinterpret_cast<const __bf16*>(b3),
+  const __bf16* a = reinterpret_cast<const __bf16*>(a3);
+  const __bf16* b = reinterpret_cast<const __bf16*>(b3);
+  if (tile == 1)
+    hipLaunchKernelGGL((k_gemm_nn32_h1<4, SC>), grid, dim3(kThreads), 0, s, m, n, k, (float)alpha, a, b,
                        (float)beta, C, ldc, tm, tn);
-    return hipGetLastError();
-  }
-  if (tile == 1) {
-    const int tm = (int)((m + 2 * kBM - 1) / (2 * kBM));
-    const dim3 grid((unsigned)(kXcds * tn * ((tm + kXcds - 1) / kXcds)));
-    if (bf16)
-      hipLaunchKernelGGL(k_gemm_nn32_tall<MODE_BF16>, grid, dim3(kThreads), 0, s, m, n, k,
-                         (float)alpha, A, lda, B, ldb, (float)beta, C, ldc, tm, tn);
-    else
-      hipLaunchKernelGGL(k_gemm_nn32_tall<MODE_F32>, grid, dim3(kThreads), 0, s, m, n, k,
-                         (float)alpha, A, lda, B, ldb, (float)beta, C, ldc, tm, tn);
-    return hipGetLastError();
-  }
-  const int tm = (int)((m + kBM - 1) / kBM);
-  const dim3 grid((unsigned)(kXcds * tn * ((tm + kXcds - 1) / kXcds)));
-  if (bf16)
-    hipLaunchKernelGGL(k_gemm_nn32<MODE_BF16>, grid, dim3(kThreads), 0, s, m, n, k, (float)alpha, A,
-                       lda, B, ldb, (float)beta, C, ldc, tm, tn);
   else
-    hipLaunchKernelGGL(k_gemm_nn32<MODE_F32>, grid, dim3(kThreads), 0, s, m, n, k, (float)alpha, A,
-                       lda, B, ldb, (float)beta, C, ldc, tm, tn);
+    hipLaunchKernelGGL((k_gemm_nn32_h1<2, SC>), grid, dim3(kThreads), 0, s, m, n, k, (float)alpha, a, b,
+                       (float)beta, C, ldc, tm, tn);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_gemm_cn32_h1(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3,
+                               const float2* B, int64_t ldb, float2* C, int64_t ldc,
+                               const double* rowscale, float2* work, hipStream_t s,
+                               const double* alpha_dev, int target, uint16_t* c3) {
+  return gemm_cn32_h1(m, n, k, alpha, a3, B, ldb, C, ldc, rowscale, work, s, alpha_dev, target, c3);
+}
+hipError_t launch_gemm_cn32_s16(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3,
+                                const bf16c* B, int64_t ldb, float2* C, int64_t ldc,
+                                const double* rowscale, float2* work, hipStream_t s,
+                                const double* alpha_dev, int target, uint16_t* c3) {
+  return gemm_cn32_h1(m, n, k, alpha, a3, B, ldb, C, ldc, rowscale, work, s, alpha_dev, target, c3);
+}
+hipError_t launch_gemm_nn32_h1(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3,
+                               const uint16_t* b3, double beta, float2* C, int64_t ldc, hipStream_t s,
+                               int tile) {
+  return gemm_nn32_h1(m, n, k, alpha, a3, b3, beta, C, ldc, s, tile);
+}
+hipError_t launch_gemm_nn32_s16(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3,
+                                const uint16_t* b3, double beta, bf16c* C, int64_t ldc, hipStream_t s,
+                                int tile) {
+  return gemm_nn32_h1(m, n, k, alpha, a3, b3, beta, C, ldc, s, tile);
+}
+
+hipError_t launch_gemm_nn32_s3(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3,
+                               const uint16_t* b3, double beta, float2* C, int64_t ldc, hipStream_t s) {
+  if (m <= 0 || n <= 0) return hipSuccess;
+  const int tn = (int)((n + kBN - 1) / kBN), tm = (int)((m + kBM - 1) / kBM);
+  const dim3 grid((unsigned)(kXcds * tn * ((tm + kXcds - 1) / kXcds)));
+  hipLaunchKernelGGL(k_gemm_nn32_s3, grid, dim3(kThreads), 0, s, m, n, k, (float)alpha,
+                     reinterpret_cast<const __bf16*>(a3), reinterpret_cast<const __bf16*>(b3),
+                     (float)beta, C, ldc, tm, tn);
   return hipGetLastError();
 }
 

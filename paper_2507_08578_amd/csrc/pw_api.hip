@@ -237,9 +237,9 @@ pw_status ham_apply32(pw_ham* h, int bf16, int64_t nb, const float2* in, int64_t
     }
     StageScope sc(c, PW_STAGE_PROJ_LP, ps);
     if (bf16)
-      HIPCHK(c, launch_gemm_cn32(1, h->nproj, nb, h->npw, alpha, h->proj32, h->npw, in, ldin,
-                                 h->cprj32, h->nproj, h->ekb_dev, h->work32, ps, coef,
-                                 h->gemm_target));
+      HIPCHK(c, launch_gemm_cn32_h1(h->nproj, nb, h->npw, alpha, h->proj3c, in, ldin, h->cprj32,
+                                    h->nproj, h->ekb_dev, h->work32, ps, coef, h->gemm_target,
+                                    h->cprj3));
     else
       HIPCHK(c, launch_gemm_cn32_s3(h->nproj, nb, h->npw, alpha, h->proj3c, in, ldin, h->cprj32,
                                     h->nproj, h->ekb_dev, h->work32, ps, coef, h->gemm_target,
@@ -267,8 +267,11 @@ pw_status ham_apply32(pw_ham* h, int bf16, int64_t nb, const float2* in, int64_t
   if (fork) HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));
   if (h->nproj > 0) {
     StageScope sc(c, PW_STAGE_NONLOCAL_LP);
-    HIPCHK(c, launch_gemm_nn32(bf16, h->npw, nb, h->nproj, 1.0, h->proj32, h->npw, h->cprj32,
-                               h->nproj, 1.0, out, ldout, s, h->nn_tile32, h->proj3, h->cprj3));
+    if (bf16)
+      HIPCHK(c, launch_gemm_nn32_h1(h->npw, nb, h->nproj, 1.0, h->proj3, h->cprj3, 1.0, out, ldout, s,
+                                    h->nn_tile32));
+    else
+      HIPCHK(c, launch_gemm_nn32_s3(h->npw, nb, h->nproj, 1.0, h->proj3, h->cprj3, 1.0, out, ldout, s));
   }
   return PW_OK;
 }
@@ -287,9 +290,9 @@ pw_status ham_apply16(pw_ham* h, int64_t nb, const bf16c* in, int64_t ldin, bf16
     return fail(c, PW_ERR_UNSUPPORTED, "BF16 block storage needs the register column kernels");
   if (h->nproj > 0) {
     StageScope sc(c, PW_STAGE_PROJ_LP);
-    HIPCHK(c, launch_gemm_cn32_s16(h->nproj, nb, h->npw, alpha, h->proj32, h->npw, in, ldin,
-                                   h->cprj32, h->nproj, h->ekb_dev, h->work32, s, coef,
-                                   h->gemm_target));
+    HIPCHK(c, launch_gemm_cn32_s16(h->nproj, nb, h->npw, alpha, h->proj3c, in, ldin, h->cprj32,
+                                   h->nproj, h->ekb_dev, h->work32, s, coef, h->gemm_target,
+                                   h->cprj3));
   }
   const Epilogue ep{alpha, beta, gamma, coef};
   for (int64_t c0 = 0; c0 < nb; c0 += h->chunk) {
@@ -311,8 +314,8 @@ pw_status ham_apply16(pw_ham* h, int64_t nb, const bf16c* in, int64_t ldin, bf16
   }
   if (h->nproj > 0) {
     StageScope sc(c, PW_STAGE_NONLOCAL_LP);
-    HIPCHK(c, launch_gemm_nn32_s16(h->npw, nb, h->nproj, 1.0, h->proj32, h->npw, h->cprj32,
-                                   h->nproj, 1.0, out, ldout, s, h->nn_tile32));
+    HIPCHK(c, launch_gemm_nn32_s16(h->npw, nb, h->nproj, 1.0, h->proj3, h->cprj3, 1.0, out, ldout, s,
+                                   h->nn_tile32));
   }
   return PW_OK;
 }
@@ -700,7 +703,6 @@ pw_status fused_setup(pw_batch* b) {
       d.kin32 = h->kin32;
       d.vs32 = h->vs32;
       d.proj = h->proj;
-      d.proj32 = h->proj32;
       d.proj3 = h->proj3;
       d.proj3c = h->proj3c;
       d.cprj3 = h->cprj3;

@@ -100,7 +100,7 @@ struct pw_ham {
   int gemm_target = 4096;    // split-K target block count of the projector product (tunable;
                              // 4096, and for FP64 above 2048: by the shape)
   int nn_tile = 0;           // workgroup tile of the tall FP64 products P C, Y Q, Y U^-1 (tunable)
-  int nn_tile32 = 0;         // the same for the FP32 / BF16 product P C (tunable)
+  int nn_tile32 = 0;         // the same for the BF16 product P C (tunable)
   bool reg_col_ok = false, reg_plane_ok = false, narrow_ok = false, narrow32_ok = false;
   bool ls32_ok = false;      // FP32 plane kernel with LDS exchanges (square P^2 planes)
   std::vector<void*> allocs;
@@ -126,8 +126,8 @@ struct pw_ham {
   float* kin32 = nullptr;
   float* vs32 = nullptr;
   float2* proj32 = nullptr;
-  // proj32 split into three bf16 terms (launch_split3 layout) for the FP32
-  // products: rows = plane waves (P C) and rows = projectors (P^H psi)
+  // proj32 split into three bf16 terms (launch_split3 layout) for the FP32 and
+  // bf16 products: rows = plane waves (P C) and rows = projectors (P^H psi)
   uint16_t* proj3 = nullptr;
   uint16_t* proj3c = nullptr;
   uint16_t* cprj3 = nullptr;   // cprj32^T in three terms (rows = bands), written by P^H psi

@@ -108,8 +108,7 @@ struct ItemDev {
   const float* kin32;
   const float* vs32;
   const cplx* proj;
-  const float2* proj32;
-  const uint16_t* proj3;               // stored three-term copies of proj32 (launch_split3):
+  const uint16_t* proj3;               // stored three-term copies of the projectors (launch_split3):
   const uint16_t* proj3c;              //   rows = plane waves / rows = projectors
   uint16_t* cprj3;                     // three-term copy of cprj32^T (rows = bands)
   const double* ekb;
@@ -448,30 +447,33 @@ hipError_t launch_gemm_cn32(int bf16, int64_t m, int64_t n, int64_t k, double al
                             int64_t lda, const float2* B, int64_t ldb, float2* C, int64_t ldc,
                             const double* rowscale, float2* work, hipStream_t s,
                             const double* alpha_dev = nullptr, int target_blocks = 0);
-// FP32 (bf16 = 0) with a3 and b3 given: A B from the stored three-term
-// copies a3 of A (rows m, contraction k) and b3 of B^T (rows n, contraction
-// k); A and B are then not read and tile has no effect.
-hipError_t launch_gemm_nn32(int bf16, int64_t m, int64_t n, int64_t k, double alpha, const float2* A,
-                            int64_t lda, const float2* B, int64_t ldb, double beta, float2* C,
-                            int64_t ldc, hipStream_t s, int tile = 0, const uint16_t* a3 = nullptr,
-                            const uint16_t* b3 = nullptr);
-// As launch_gemm_cn32 with bf16 = 0, A given as the stored three-term copy a3
-// of A^T (rows m, contraction k); with c3, the reduction also stores the
-// three-term copy of C^T (rows n, contraction m) for launch_gemm_nn32.
+// As launch_gemm_cn32 with A given as the stored three-term copy a3 of A^T
+// (rows m, contraction k): FP32 operands (_s3) or bf16 (_h1; _s16 with B a
+// bf16-pair block).  With c3, the reduction also stores the three-term copy of
+// C^T (rows n, contraction m).
 hipError_t launch_gemm_cn32_s3(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3,
                                const float2* B, int64_t ldb, float2* C, int64_t ldc,
                                const double* rowscale, float2* work, hipStream_t s,
                                const double* alpha_dev, int target_blocks, uint16_t* c3);
-// bf16 operands with the block operand stored as bf16 pairs: A^H B with B a
-// bf16-pair block (split-K partials and result complex64, as launch_gemm_cn32
-// with bf16 = 1), and C (bf16 pairs) = alpha A B + beta C with A, B complex64.
-hipError_t launch_gemm_cn32_s16(int64_t m, int64_t n, int64_t k, double alpha, const float2* A,
-                                int64_t lda, const bf16c* B, int64_t ldb, float2* C, int64_t ldc,
+hipError_t launch_gemm_cn32_h1(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3,
+                               const float2* B, int64_t ldb, float2* C, int64_t ldc,
+                               const double* rowscale, float2* work, hipStream_t s,
+                               const double* alpha_dev, int target_blocks, uint16_t* c3);
+hipError_t launch_gemm_cn32_s16(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3,
+                                const bf16c* B, int64_t ldb, float2* C, int64_t ldc,
                                 const double* rowscale, float2* work, hipStream_t s,
-                                const double* alpha_dev = nullptr, int target_blocks = 0);
-hipError_t launch_gemm_nn32_s16(int64_t m, int64_t n, int64_t k, double alpha, const float2* A,
-                                int64_t lda, const float2* B, int64_t ldb, double beta, bf16c* C,
-                                int64_t ldc, hipStream_t s, int tile = 0);
+                                const double* alpha_dev, int target_blocks, uint16_t* c3);
+// C = alpha A B + beta C from the stored three-term copies a3 of A (rows m,
+// contraction k) and b3 of B^T (rows n, contraction k): FP32 operands (_s3) or
+// bf16 (_h1; _s16 with C bf16 pairs; tile 1: 128-row tiles).
+hipError_t launch_gemm_nn32_s3(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3,
+                               const uint16_t* b3, double beta, float2* C, int64_t ldc, hipStream_t s);
+hipError_t launch_gemm_nn32_h1(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3,
+                               const uint16_t* b3, double beta, float2* C, int64_t ldc, hipStream_t s,
+                               int tile);
+hipError_t launch_gemm_nn32_s16(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3,
+                                const uint16_t* b3, double beta, bf16c* C, int64_t ldc, hipStream_t s,
+                                int tile);
 // Stored three-term copies: X3 holds X (rows x k; element (r, c) at
 // X[r sr + c sk]) split exactly into three bf16 terms per real part, in
 // chunks of 32 contraction values (six planes of 32 bf16 per chunk, a row's
