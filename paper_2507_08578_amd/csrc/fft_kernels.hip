@@ -31,6 +31,12 @@ namespace {
 
 constexpr int kThreads = 256;
 
+// i / n for 0 <= i < 2^20 by a reciprocal of n, inv = div_inv(n): the half keeps
+// the quotient further from the next integer than its rounding reaches.  An
+// integer division takes about 30 instructions, a pass of a transform not many more.
+__device__ __forceinline__ float div_inv(int n) { return __builtin_amdgcn_rcpf((float)n); }
+__device__ __forceinline__ int div_by(int i, float inv) { return (int)(((float)i + 0.5f) * inv); }
+
 // One Stockham radix-R pass over `ntr` transforms of length n stored at
 // buf[t*trs + i], in place.  ns = product of the radices already applied.
 // Stockham step: butterfly j reads x[j + r*n/R], twiddles by
@@ -38,8 +44,9 @@ constexpr int kThreads = 256;
 template <int R, int S, class C>
 __device__ void stockham_pass(C* buf, int ntr, int trs, int n, int ns, const C* __restrict__ tw) {
   const int nbf = n / R;            // butterflies per transform
-  const int rest = nbf / ns;        // n / (ns R)
-  const int group = blockDim.x / nbf;
+  const float inv_nbf = div_inv(nbf), inv_ns = div_inv(ns);
+  const int rest = div_by(nbf, inv_ns);        // n / (ns R)
+  const int group = div_by(blockDim.x, inv_nbf);
   for (int t0 = 0; t0 < ntr; t0 += group) {
     const int cnt = min(group, ntr - t0);
     const int u = threadIdx.x;
@@ -47,9 +54,10 @@ __device__ void stockham_pass(C* buf, int ntr, int trs, int n, int ns, const C* 
     C v[R];
     int t = 0, j = 0, k = 0;
     if (act) {
-      t = t0 + u / nbf;
-      j = u - (u / nbf) * nbf;
-      k = j % ns;
+      t = div_by(u, inv_nbf);
+      j = u - t * nbf;
+      t += t0;
+      k = j - div_by(j, inv_ns) * ns;
       const C* b = buf + (size_t)t * trs;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -135,8 +143,9 @@ __device__ __forceinline__ void col_inv_body(const PL& P, int ct, const C* __res
   __syncthreads();
   fft_lds<+1>(lds, ncl, trs, P.ax3);
   C* dst = T + (size_t)b * P.n3 * P.ldt + c0;
+  const float inv = div_inv(ncl);
   for (int i = threadIdx.x; i < ncl * P.n3; i += blockDim.x) {
-    const int j3 = i / ncl, lc = i - j3 * ncl;
+    const int j3 = div_by(i, inv), lc = i - j3 * ncl;
     dst[(size_t)j3 * P.ldt + lc] = lds[lc * trs + j3];
   }
 }
@@ -156,6 +165,7 @@ __device__ __forceinline__ void plane_body(const PL& P, int rb, const real_t<C>*
   const int trsr = P.n1 + 1;
   C* E = lds;
   C* Rw = lds + P.xr * trse;
+  const float inv_xr = div_inv(P.xr), inv_n1 = div_inv(P.n1);
   C* tp = T + (size_t)b * P.n3 * P.ldt + (size_t)j3 * P.ldt;
   for (int i = threadIdx.x; i < P.xr * trse; i += blockDim.x) E[i] = czero<C>();
   __syncthreads();
@@ -168,19 +178,19 @@ __device__ __forceinline__ void plane_body(const PL& P, int rb, const real_t<C>*
     for (int i = threadIdx.x; i < nr * trsr; i += blockDim.x) Rw[i] = czero<C>();
     __syncthreads();
     for (int i = threadIdx.x; i < nr * P.xr; i += blockDim.x) {
-      const int r = i / P.xr, e = i - r * P.xr;
+      const int r = div_by(i, inv_xr), e = i - r * P.xr;
       Rw[r * trsr + P.ext_m1[e]] = E[e * trse + r0 + r];
     }
     __syncthreads();
     fft_lds<+1>(Rw, nr, trsr, P.ax1);
     for (int i = threadIdx.x; i < nr * P.n1; i += blockDim.x) {
-      const int r = i / P.n1, j1 = i - r * P.n1;
+      const int r = div_by(i, inv_n1), j1 = i - r * P.n1;
       Rw[r * trsr + j1] = cscale(Rw[r * trsr + j1], vp[(size_t)(r0 + r) * P.n1 + j1]);
     }
     __syncthreads();
     fft_lds<-1>(Rw, nr, trsr, P.ax1);
     for (int i = threadIdx.x; i < nr * P.xr; i += blockDim.x) {
-      const int r = i / P.xr, e = i - r * P.xr;
+      const int r = div_by(i, inv_xr), e = i - r * P.xr;
       E[e * trse + r0 + r] = Rw[r * trsr + P.ext_m1[e]];
     }
     __syncthreads();
@@ -207,6 +217,7 @@ k_density_plane(PlanArgs P, int rb, const double2* __restrict__ T, int nbc,
   double2* E = reinterpret_cast<double2*>(lds_raw);
   const int trse = P.n2 + 1, trsr = P.n1 + 1;
   double2* Rw = E + P.xr * trse;
+  const float inv_xr = div_inv(P.xr), inv_n1 = div_inv(P.n1);
   const int j3 = blockIdx.x, g = blockIdx.y;
   double* pp = part + ((size_t)g * P.n3 + j3) * P.n2 * P.n1;
   if (g >= nbc && !add) {   // a group without bands in the first chunk starts from zero
@@ -229,13 +240,13 @@ k_density_plane(PlanArgs P, int rb, const double2* __restrict__ T, int nbc,
       for (int i = threadIdx.x; i < nr * trsr; i += blockDim.x) Rw[i] = czero<double2>();
       __syncthreads();
       for (int i = threadIdx.x; i < nr * P.xr; i += blockDim.x) {
-        const int r = i / P.xr, e = i - r * P.xr;
+        const int r = div_by(i, inv_xr), e = i - r * P.xr;
         Rw[r * trsr + P.ext_m1[e]] = E[e * trse + r0 + r];
       }
       __syncthreads();
       fft_lds<+1>(Rw, nr, trsr, P.ax1);
       for (int i = threadIdx.x; i < nr * P.n1; i += blockDim.x) {
-        const int r = i / P.n1, j1 = i - r * P.n1;
+        const int r = div_by(i, inv_n1), j1 = i - r * P.n1;
         const double2 v = Rw[r * trsr + j1];
         double* d = pp + (size_t)(r0 + r) * P.n1 + j1;
         *d = (fresh ? 0.0 : *d) + wb * (v.x * v.x + v.y * v.y);
@@ -266,8 +277,9 @@ __device__ __forceinline__ void col_fwd_body(const PL& P, int ct, const C* __res
   const int ncl = min(ct, P.ncols - c0);
   const int trs = P.n3 + 1;
   const C* srcT = T + (size_t)b * P.n3 * P.ldt + c0;
+  const float inv = div_inv(ncl);
   for (int i = threadIdx.x; i < ncl * P.n3; i += blockDim.x) {
-    const int j3 = i / ncl, lc = i - j3 * ncl;
+    const int j3 = div_by(i, inv), lc = i - j3 * ncl;
     lds[lc * trs + j3] = srcT[(size_t)j3 * P.ldt + lc];
   }
   __syncthreads();
