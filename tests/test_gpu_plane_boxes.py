@@ -96,3 +96,15 @@ def test_many_planes_per_workgroup(pw, ctx, box, nb):
     pick = [0, 1, nb // 2, nb - 2, nb - 1]
     err = rel_err(H[pick], oracle.apply_h(oh, X[pick].T).T)
     assert err < 1e-12, err
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_autotune_keeps_the_register_planes(pw, ctx, prec):
+    """reg_plane = 0 would select the two-factor planes for H*psi, which the rule
+    does by itself, and leave Rayleigh-Ritz above 64 bands the general ones."""
+    box, nb = (48, 48, 24), 70
+    g, recip, v, oh = problem(box, frac=0.2, seed=3)
+    ham = pw.Hamiltonian(ctx, g, recip, oh.kred, box, to_dev(v), None, None, nb, low_prec=True)
+    assert ham.get_tuning()["reg_plane"] == 1
+    ham.autotune(prec, nb, reps=1)
+    assert ham.get_tuning()["reg_plane"] == 1
