@@ -90,12 +90,22 @@ COUNTER_FILES = {
 }
 
 
+TWO_FACTOR = {16, 18, 20, 24, 25, 27, 30, 32, 36, 40, 45, 48, 50, 54, 60, 64, 72, 75, 80, 81, 90, 96,
+              100, 108, 120, 128, 135, 144, 150, 160}
+
+
 def plane_kernel(ham, prec):
-    """Name of the plane kernel the handle's tuning selects for this precision."""
-    t = ham.get_tuning()
-    if prec != "fp64" and t["reg_plane"] and t["plane_variant32"] == 2:
+    """Name of the plane kernel that the handle's tuning and the library's rule
+    on the box select for this precision."""
+    t, (n1, n2, _) = ham.get_tuning(), ham.box
+    lp = prec != "fp64"
+    variant = t["plane_variant32" if lp else "plane_variant"]
+    if lp and t["reg_plane"] and variant == 2:
         return "k_plane_ls"
-    return "k_plane_reg" if t["reg_plane"] else "k_plane"
+    wins = n1 >= 36 and n1 not in (128, 160) if lp else n1 in (36, 72)
+    if t["reg_plane"] and not (variant == 0 and wins):
+        return "k_plane_reg"
+    return "k_plane_pq" if {n1, n2} <= TWO_FACTOR else "k_plane"
 
 
 def measured_traffic(config, prec, stage, kernel, bands_per_launch):
@@ -165,12 +175,11 @@ def roofline(stages, steps, w, ham, nb, prec, config=None):
         on_bf16 = prec in ("bf16", "fp32")
         peak = PEAK["fp64_mfma" if prec == "fp64" else ("bf16_mfma" if on_bf16 else "fp32_mfma")]
         ach = fl / (avg_ms * 1e-3) / 1e12
-        mode = "" if prec == "fp64" else ("<F32>" if prec == "fp32" else "<BF16>")
         sx = "" if prec == "fp64" else "32"
         extra = {}
         if dom == "proj":
-            key = f"k_gemm_cn{sx}"
-            kname = f"k_gemm_cn{sx}{mode} + k_splitk_reduce{sx} (P^H psi, split-K, KB scale)"
+            key = "k_gemm_cn" if prec == "fp64" else "k_gemm_cn32_h1"
+            kname = f"{key} + k_splitk_reduce{sx} (P^H psi, split-K, KB scale)"
             if prec == "fp32":
                 key = "k_gemm_cn32_s3"
                 kname = ("k_gemm_cn32_s3 + k_splitk_reduce32 (P^H psi, split-K, KB scale; P as "
@@ -185,8 +194,9 @@ def roofline(stages, steps, w, ham, nb, prec, config=None):
                      "executed_TFLOPs": 6.0 * ach, "executed_frac": 6.0 * ach / peak}
         else:
             tall = ham.get_tuning()["nn_tile" if prec == "fp64" else "nn_tile32"] == 1
-            key = f"k_gemm_nn{sx}{'_tall' if tall else ''}"
-            kname = f"{key}{mode} (H psi += P C)"
+            key = (f"k_gemm_nn{'_tall' if tall else ''}" if prec == "fp64"
+                   else f"k_gemm_nn32_h1<{4 if tall else 2}>")
+            kname = f"{key} (H psi += P C)"
         return dict({"kernel": kname, "bound": "mfma", "achieved": ach, "peak": peak,
                      "unit": "TFLOP/s", "frac": ach / peak,
                      "traffic": measured_traffic(config, prec, dom, key, 1),

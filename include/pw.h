@@ -123,7 +123,8 @@ pw_status pw_ctx_set_sweep_limit(pw_ctx* ctx, int32_t max_sweeps);
  * Concurrency inside H psi (default off): the projection product P^H psi
  * runs on a second stream of the context, forked from and joined back to
  * the context's stream by events, so it overlaps the FFT route of the same
- * application; P C waits for both.  Results are bit-identical either way;
+ * application; P C waits for both (few projectors in FP64: no second
+ * stream, one launch forms both).  Results are bit-identical either way;
  * graph capture sees the fork and join.  Off: everything on one stream
  * (faster on the benchmarked cell, where the persistent plane kernel and
  * the projection each fill the compute units).  Applies to calls issued on
@@ -385,7 +386,7 @@ typedef struct {
   int32_t chunk;          /* bands per FFT launch, [1, the handle's buffer]                  */
   int32_t gemm_blocks;    /* split-K target block count of P^H psi, [1, 4096] (FP64: <= 2048) */
   int32_t nn_tile;        /* tall FP64 products P C, Y Q, Y U^-1: 0 64x64, 1 128x64 tiles    */
-  int32_t nn_tile32;      /* the same choice for the FP32 / BF16 product P C                 */
+  int32_t nn_tile32;      /* the same choice for the BF16 product P C                        */
   double ms;              /* pw_ham_autotune: median time of one H*psi of nb bands           */
 } pw_tuning;
 
@@ -538,8 +539,9 @@ typedef enum {
   PW_STAGE_FFT_COL_INV = 0,  /* scatter + backward transform along N3 (sphere columns)   */
   PW_STAGE_FFT_PLANE = 1,    /* N2/N1 backward, x V, N1/N2 forward, per z-plane            */
   PW_STAGE_FFT_COL_FWD = 2,  /* forward along N3 + gather + kinetic + recurrence epilogue */
-  PW_STAGE_PROJ = 3,         /* cprj C = P^H psi (split-K) + reduction x E_KB               */
-  PW_STAGE_NONLOCAL = 4,     /* H psi += P C                                               */
+  PW_STAGE_PROJ = 3,         /* cprj C = P^H psi (split-K) + reduction x E_KB; few projectors
+                                in FP64: in the launches of FFT_COL_INV                    */
+  PW_STAGE_NONLOCAL = 4,     /* H psi += P C; few projectors in FP64: in FFT_COL_FWD       */
   PW_STAGE_GRAM = 5,         /* Y^H Y and Y^H W                                            */
   PW_STAGE_CHOL = 6,         /* Cholesky + triangular inverse                              */
   PW_STAGE_ROTATE = 7,       /* Y U^{-1}, Y Q, W Q                                         */

@@ -829,7 +829,7 @@ __device__ __forceinline__ int bj_index(int i, int I, int J) {
 // leave in LDS, to V (rows Qb and Qb + kBJ of pair P).  With V, and the circle
 // method's index arithmetic, on the chain's own wavefronts a sweep of 31 rounds
 // took 31.4 us (k_bj_inner) and a fused step 40.4 us at n = 160 and 45.5 us at
-// n = 448; as it is, 24.2, 32.2 and 36.6 us.
+// n = 512; as it is, 24.2, 32.2 and 36.6 us.
 constexpr int kBJHalf = kBJ * kBJ;               // threads of the A part
 constexpr int kBJThreads = 2 * kBJHalf;
 constexpr int kBJA = 4 * kBJHalf;                // entries of one copy of A
