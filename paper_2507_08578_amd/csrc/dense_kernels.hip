@@ -458,6 +458,7 @@ constexpr int kJacMidMax = 46;   // two copies of A and V: 135 KiB of LDS
 struct RotS {
   double cs, t;     // cosine; change of the diagonal (0 where no rotation)
   cplx s;           // sn ph
+  bool on;          // false: identity (c zero, or NaN)
 };
 // y = 1/sqrt(x): one third-order step from the hardware's estimate, with the
 // rounding of x y carried along (correct to about half a unit)
@@ -478,6 +479,7 @@ __device__ __forceinline__ RotS make_rot_s(double a, double b, cplx c) {
   const double r = q * rsqrt_h(q), p = fabs(d) + r;
   const double y = rsqrt_h(fma(p, p, m4)), y2 = copysign(2.0 * y, d);
   RotS R;
+  R.on = on;
   R.cs = on ? p * y : 1.0;
   R.t = on ? (0.5 * m4 * r) * (y * y2) : 0.0;
   R.s = on ? make_double2(c.x * y2, c.y * y2) : make_double2(0.0, 0.0);
@@ -590,9 +592,11 @@ __device__ __forceinline__ void jacobi_mid_body(int n, const cplx* __restrict__ 
           x12 = cadd(cscale(m12, RP.cs), cmul(p12, m22));
           x21 = cadd(cmul(p21, m11), cscale(m21, RP.cs));
           x22 = cadd(cmul(p21, m12), cscale(m22, RP.cs));
-          if (P == Qb) {
-            x11 = make_double2(ap - RP.t, 0.0);
-            x22 = make_double2(aq + RP.t, 0.0);
+          // an identity leaves the block as it is: a NaN stays, and the solve
+          // then ends without convergence instead of losing it
+          if (P == Qb && RQ.on) {
+            x11 = make_double2(ap - RQ.t, 0.0);
+            x22 = make_double2(aq + RQ.t, 0.0);
             x12 = x21 = make_double2(0.0, 0.0);
           }
           B[dst[0]] = x11;
