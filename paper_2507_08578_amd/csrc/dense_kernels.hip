@@ -481,7 +481,7 @@ __device__ __forceinline__ RotS make_rot_s(double a, double b, cplx c) {
   RotS R;
   R.on = on;
   R.cs = on ? p * y : 1.0;
-  R.t = on ? (0.5 * m4 * r) * (y * y2) : 0.0;
+  R.t = on ? (0.5 * m4 * y2) * (r * y) : 0.0;   // no factor beyond |c|^2 in size
   R.s = on ? make_double2(c.x * y2, c.y * y2) : make_double2(0.0, 0.0);
   return R;
 }
