@@ -23,6 +23,7 @@
 #include "pw_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
@@ -288,17 +289,41 @@ __device__ __forceinline__ void gemm_cn32_b3_body(int64_t M, int64_t N, int64_t 
       }
 }
 
+// Products of few tiles (split_plan32_wide): the FP32 sums stay over `sub` values
+// of K, as in a split of its own each, and the workgroup adds them up in FP64.
+struct WideSum {
+  double re[2][2][4], im[2][2][4];
+  int64_t next;   // where the current FP32 sum ends
+  __device__ __forceinline__ void start(int64_t kb, int64_t sub) {
+    next = kb + sub;
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+      for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) re[ti][tj][r] = im[ti][tj][r] = 0.0;
+  }
+  __device__ __forceinline__ void add(int ti, int tj, int r, float x, float y) {
+    re[ti][tj][r] += (double)x;
+    im[ti][tj][r] += (double)y;
+  }
+};
+
 // Partial (split z over K) A^H B with A given as its stored three-term copy
 // A3 (rows = the M columns of A, contraction K; the chunk layout above) and B
 // (K x N, ldb) complex64, split per stage: thread tid stages chunk row tid / 4
 // of A3 and column tid / 4 of B, K 8 (tid % 4) .. + 7 of the stage.  The same
 // products as gemm_cn32_b3_body in the same order, so the same result.
 // Columns j >= N are read from column N - 1 (they feed only outputs that are
-// not stored); K beyond ke reads zero from B.
+// not stored); K beyond ke reads zero from B.  WIDE: FP64 partials (WideSum).
+template <bool WIDE>
+using partial_t = typename std::conditional<WIDE, double2, float2>::type;
+template <bool WIDE>
 __device__ __forceinline__ void gemm_cn32_s3_body(int64_t M, int64_t N, int64_t K, int64_t ksplit,
-                                                  const __bf16* __restrict__ A3,
+                                                  int64_t sub, const __bf16* __restrict__ A3,
                                                   const float2* __restrict__ B, int64_t ldb,
-                                                  float2* __restrict__ out, int bx, int by, int bz) {
+                                                  partial_t<WIDE>* __restrict__ out, int bx, int by,
+                                                  int bz) {
   __shared__ __align__(16) __bf16 LA[6 * kB3Plane];
   __shared__ __align__(16) __bf16 LB[6 * kB3Plane];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -334,6 +359,8 @@ __device__ __forceinline__ void gemm_cn32_s3_body(int64_t M, int64_t N, int64_t 
     }
     pb += kB3K;
   };
+  WideSum w;
+  if constexpr (WIDE) w.start(kb, sub);
   if (kb < ke) fetch(kb);
   for (int64_t k0 = kb; k0 < ke; k0 += kB3K) {
     s3_put(LA, row, k8, ra);
@@ -361,9 +388,24 @@ __device__ __forceinline__ void gemm_cn32_s3_body(int64_t M, int64_t N, int64_t 
         acc[1][ti][tj] = mfma6(a[ti][0], b[tj][1], acc[1][ti][tj]);
         acc[2][ti][tj] = mfma6(a[ti][1], b[tj][0], acc[2][ti][tj]);
       }
+    if constexpr (WIDE) {
+      if (k0 + kB3K >= min(w.next, ke)) {
+        w.next += sub;
+#pragma unroll
+        for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+          for (int tj = 0; tj < 2; ++tj) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              w.add(ti, tj, r, acc[0][ti][tj][r], acc[1][ti][tj][r] - acc[2][ti][tj][r]);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) f4zero(acc[q][ti][tj]);
+          }
+      }
+    }
     __syncthreads();
   }
-  float2* o = out + (int64_t)bz * M * N;
+  partial_t<WIDE>* o = out + (int64_t)bz * M * N;
 #pragma unroll
   for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
@@ -372,8 +414,10 @@ __device__ __forceinline__ void gemm_cn32_s3_body(int64_t M, int64_t N, int64_t 
       for (int r = 0; r < 4; ++r) {
         const int64_t i = i0 + wi * 32 + ti * 16 + 4 * lk + r;
         const int64_t j = j0 + wj * 32 + tj * 16 + lr;
-        if (i < M && j < N)
-          o[i + j * M] = make_float2(acc[0][ti][tj][r], acc[1][ti][tj][r] - acc[2][ti][tj][r]);
+        if (i < M && j < N) {
+          if constexpr (WIDE) o[i + j * M] = make_double2(w.re[ti][tj][r], w.im[ti][tj][r]);
+          else o[i + j * M] = make_float2(acc[0][ti][tj][r], acc[1][ti][tj][r] - acc[2][ti][tj][r]);
+        }
       }
 }
 
@@ -611,11 +655,12 @@ __device__ __forceinline__ void h1_pack(const float2 (&x)[8], bf8& re, bf8& im) 
 // Partial (split z over K) A^H B, A3 and B as in gemm_cn32_s3_body, B complex64
 // (rounded as it is staged) or bf16 pairs.  Chunks past ke are neither read nor
 // multiplied.
-template <class SB>
+template <class SB, bool WIDE>
 __device__ __forceinline__ void gemm_cn32_h1_body(int64_t M, int64_t N, int64_t K, int64_t ksplit,
-                                                  const __bf16* __restrict__ A3,
+                                                  int64_t sub, const __bf16* __restrict__ A3,
                                                   const SB* __restrict__ B, int64_t ldb,
-                                                  float2* __restrict__ out, int bx, int by, int bz) {
+                                                  partial_t<WIDE>* __restrict__ out, int bx, int by,
+                                                  int bz) {
   __shared__ __align__(16) __bf16 LA[2 * kH1Chunks * kB3Plane];
   __shared__ __align__(16) __bf16 LB[2 * kH1Chunks * kB3Plane];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -656,6 +701,8 @@ __device__ __forceinline__ void gemm_cn32_h1_body(int64_t M, int64_t N, int64_t 
     pa += kH1Chunks * kS3Chunk;
     pb += kH1Chunks * kB3K;
   };
+  WideSum w;
+  if constexpr (WIDE) w.start(kb, sub);
   if (kb < ke) fetch(kb);
   for (int64_t k0 = kb; k0 < ke; k0 += kH1Chunks * kB3K) {
 #pragma unroll
@@ -672,11 +719,27 @@ __device__ __forceinline__ void gemm_cn32_h1_body(int64_t M, int64_t N, int64_t 
     const int64_t k1 = k0 + kH1Chunks * kB3K;
     if (k1 < ke) fetch(k1);
 #pragma unroll
-    for (int u = 0; u < kH1Chunks; ++u)
-      if (k0 + u * kB3K < ke) h1_step<true, 2, 64>(LA, LB, u, wi * 32, wj * 32, lr, lk, ar, ai);
+    for (int u = 0; u < kH1Chunks; ++u) {
+      if (k0 + u * kB3K >= ke) break;
+      h1_step<true, 2, 64>(LA, LB, u, wi * 32, wj * 32, lr, lk, ar, ai);
+      if constexpr (WIDE) {
+        if (k0 + (u + 1) * kB3K >= min(w.next, ke)) {
+          w.next += sub;
+#pragma unroll
+          for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+            for (int tj = 0; tj < 2; ++tj) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r) w.add(ti, tj, r, ar[ti][tj][r], ai[ti][tj][r]);
+              f4zero(ar[ti][tj]);
+              f4zero(ai[ti][tj]);
+            }
+        }
+      }
+    }
     __syncthreads();
   }
-  float2* o = out + (int64_t)bz * M * N;
+  partial_t<WIDE>* o = out + (int64_t)bz * M * N;
 #pragma unroll
   for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
@@ -685,7 +748,10 @@ __device__ __forceinline__ void gemm_cn32_h1_body(int64_t M, int64_t N, int64_t 
       for (int r = 0; r < 4; ++r) {
         const int64_t i = i0 + wi * 32 + ti * 16 + 4 * lk + r;
         const int64_t j = j0 + wj * 32 + tj * 16 + lr;
-        if (i < M && j < N) o[i + j * M] = make_float2(ar[ti][tj][r], ai[ti][tj][r]);
+        if (i < M && j < N) {
+          if constexpr (WIDE) o[i + j * M] = make_double2(w.re[ti][tj][r], w.im[ti][tj][r]);
+          else o[i + j * M] = make_float2(ar[ti][tj][r], ai[ti][tj][r]);
+        }
       }
 }
 
@@ -846,30 +912,34 @@ k_gemm_cn32(int64_t M, int64_t N, int64_t K, int64_t ksplit, const float2* __res
   gemm_cn32_body<MODE>(M, N, K, ksplit, A, lda, B, ldb, out, bx, by, bz);
 }
 
-__global__ void __launch_bounds__(kThreads)
-k_gemm_cn32_s3(int64_t M, int64_t N, int64_t K, int64_t ksplit, const __bf16* __restrict__ A3,
-               const float2* __restrict__ B, int64_t ldb, float2* __restrict__ out, int tiles_m,
-               int tiles_n, int nsplit) {
+// WIDE: two wavefronts per SIMD stay resident (without the bound the FP64 sums and
+// accumulation registers leave room for one: 43.7 instead of 31.1 us)
+template <bool WIDE>
+__global__ void __launch_bounds__(kThreads, WIDE ? 2 : 1)
+k_gemm_cn32_s3(int64_t M, int64_t N, int64_t K, int64_t ksplit, int64_t sub,
+               const __bf16* __restrict__ A3, const float2* __restrict__ B, int64_t ldb,
+               partial_t<WIDE>* __restrict__ out, int tiles_m, int tiles_n, int nsplit) {
   int bx, by, bz;
   if (!xcd_split_tile(blockIdx.x, tiles_m, tiles_n, nsplit, &bx, &by, &bz)) return;
-  gemm_cn32_s3_body(M, N, K, ksplit, A3, B, ldb, out, bx, by, bz);
+  gemm_cn32_s3_body<WIDE>(M, N, K, ksplit, sub, A3, B, ldb, out, bx, by, bz);
 }
 
-template <class SB>
-__global__ void __launch_bounds__(kThreads)
-k_gemm_cn32_h1(int64_t M, int64_t N, int64_t K, int64_t ksplit, const __bf16* __restrict__ A3,
-               const SB* __restrict__ B, int64_t ldb, float2* __restrict__ out, int tiles_m,
-               int tiles_n, int nsplit) {
+template <class SB, bool WIDE>
+__global__ void __launch_bounds__(kThreads, WIDE ? 2 : 1)
+k_gemm_cn32_h1(int64_t M, int64_t N, int64_t K, int64_t ksplit, int64_t sub,
+               const __bf16* __restrict__ A3, const SB* __restrict__ B, int64_t ldb,
+               partial_t<WIDE>* __restrict__ out, int tiles_m, int tiles_n, int nsplit) {
   int bx, by, bz;
   if (!xcd_split_tile(blockIdx.x, tiles_m, tiles_n, nsplit, &bx, &by, &bz)) return;
-  gemm_cn32_h1_body<SB>(M, N, K, ksplit, A3, B, ldb, out, bx, by, bz);
+  gemm_cn32_h1_body<SB, WIDE>(M, N, K, ksplit, sub, A3, B, ldb, out, bx, by, bz);
 }
 
 // C[i + j ldc] = alpha rowscale[i] sum_z work[z][i + j M] (FP64 sum, fixed order), rounded;
 // with c3, also the stored three-term copy of the rounded C^T (rows = the N
 // columns of C, contraction M: the B operand of gemm_nn32_s3_body).
+template <class W>
 __device__ __forceinline__ void splitk_reduce32_body(int64_t M, int64_t N, int nsplit,
-                                                     const float2* __restrict__ work, double alpha,
+                                                     const W* __restrict__ work, double alpha,
                                                      const double* __restrict__ alpha_dev,
                                                      const double* __restrict__ rowscale,
                                                      float2* __restrict__ C, int64_t ldc,
@@ -897,7 +967,8 @@ __device__ __forceinline__ void splitk_reduce32_body(int64_t M, int64_t N, int n
   }
 }
 
-__global__ void k_splitk_reduce32(int64_t M, int64_t N, int nsplit, const float2* __restrict__ work,
+template <class W>
+__global__ void k_splitk_reduce32(int64_t M, int64_t N, int nsplit, const W* __restrict__ work,
                                   double alpha, const double* __restrict__ alpha_dev,
                                   const double* __restrict__ rowscale, float2* __restrict__ C,
                                   int64_t ldc, __bf16* __restrict__ c3) {
@@ -908,23 +979,16 @@ struct SplitPlan {
   int64_t tiles_m, tiles_n, nsplit, ksplit;
 };
 
-// Workgroups aimed at, as in gemm_kernels.hip: outside [1, kTargetBlocks), the
-// default, by the tiles (256 x 160 outputs over 37073 values, FP32: 128 us at
-// 4096, 105 at 2048, 92 at 512, 108 at 384; 192 x 117 over 16346: 46, 46, 32, 33).
-constexpr int kFewTiles = 32, kFewTilesTarget = 512;
-__host__ __device__ inline int split_target32(int target, int64_t tiles) {
-  if (target >= 1 && target < kTargetBlocks) return target;
-  return tiles <= kFewTiles ? kFewTilesTarget : kTargetBlocks;
-}
-
-template <int MODE>
+// Splits for `target` workgroups (default, or out of range: kTargetBlocks).  A
+// split's FP32 sum is 64 values of K and up: what keeps the error of a long
+// contraction near that of its operands.
 __host__ __device__ inline SplitPlan split_plan32(int64_t m, int64_t n, int64_t k, int target) {
   constexpr int Kc = 32;   // complex K per LDS stage of both P^H psi kernels
+  if (target < 1 || target > kTargetBlocks) target = kTargetBlocks;
   SplitPlan p;
   p.tiles_m = (m + kBM - 1) / kBM;
   p.tiles_n = (n + kBN - 1) / kBN;
   const int64_t tiles = p.tiles_m * p.tiles_n;
-  target = split_target32(target, tiles);
   int64_t want = (target + tiles - 1) / tiles;
   // at least two K stages per split (short splits keep small products latency-light)
   const int64_t maxs = (k + Kc * 2 - 1) / (Kc * 2) > 1 ? (k + Kc * 2 - 1) / (Kc * 2) : 1;
@@ -939,6 +1003,31 @@ __host__ __device__ inline SplitPlan split_plan32(int64_t m, int64_t n, int64_t 
   return p;
 }
 
+// At the default target, outputs of few tiles: one workgroup takes `per` of those
+// splits, which it adds up in FP64 (WideSum), so the sums are what they are above
+// while fewer partials are written and read (kFewTilesTarget workgroups).  H psi
+// at 256 x 160 outputs over 37073 values, bf16: 665 -> 624 us (product 54 -> 42), at
+// 192 x 117 over 16346, FP32: 206 -> 196 us.  FP32 sums over the whole of a
+// workgroup's range would take 611 and 190 us, but their errors are up to 2.4
+// times as large (37073 values, 12 tiles: 1.0e-7 instead of 4.2e-8).
+struct WidePlan {
+  SplitPlan p;
+  int64_t sub, per;
+};
+inline WidePlan split_plan32_wide(int64_t m, int64_t n, int64_t k, int target) {
+  WidePlan w{split_plan32(m, n, k, target), 0, 1};
+  SplitPlan& p = w.p;
+  w.sub = p.ksplit;
+  const int64_t tiles = p.tiles_m * p.tiles_n;
+  if ((target >= 1 && target < kTargetBlocks) || tiles > kFewTiles) return w;
+  int64_t want = (kFewTilesTarget + tiles - 1) / tiles;
+  if (want >= 2 * kXcds) want -= want % kXcds;
+  w.per = (p.nsplit + want - 1) / want;
+  p.ksplit *= w.per;
+  p.nsplit = (p.nsplit + w.per - 1) / w.per;
+  return w;
+}
+
 // ---- fused-batch products (FP32 / bf16 operands): P^H X into work32, reduced into
 // cprj32; X += P cprj32
 template <int MODE>
@@ -947,22 +1036,23 @@ kb_gemm_cn32(const ItemDev* __restrict__ D, int sel_b, int nsplit_max) {
   const int item = blockIdx.z / nsplit_max, zs = blockIdx.z - item * nsplit_max;
   const ItemDev& d = D[item];
   if (d.nproj <= 0) return;
-  const SplitPlan p = split_plan32<MODE>(d.nproj, d.nb, d.npw, d.gemm_target);
+  const SplitPlan p = split_plan32(d.nproj, d.nb, d.npw, d.gemm_target);
   if (zs >= p.nsplit || (int64_t)blockIdx.y >= p.tiles_m || (int64_t)blockIdx.x >= p.tiles_n) return;
   if constexpr (MODE == MODE_F32)
-    gemm_cn32_s3_body(d.nproj, d.nb, d.npw, p.ksplit, reinterpret_cast<const __bf16*>(d.proj3c),
-                      item_blk32(d, sel_b), d.npw, d.work32, blockIdx.x, blockIdx.y, zs);
+    gemm_cn32_s3_body<false>(d.nproj, d.nb, d.npw, p.ksplit, 0,
+                             reinterpret_cast<const __bf16*>(d.proj3c), item_blk32(d, sel_b), d.npw,
+                             d.work32, blockIdx.x, blockIdx.y, zs);
   else
-    gemm_cn32_h1_body<float2>(d.nproj, d.nb, d.npw, p.ksplit,
-                              reinterpret_cast<const __bf16*>(d.proj3c), item_blk32(d, sel_b), d.npw,
-                              d.work32, blockIdx.x, blockIdx.y, zs);
+    gemm_cn32_h1_body<float2, false>(d.nproj, d.nb, d.npw, p.ksplit, 0,
+                                     reinterpret_cast<const __bf16*>(d.proj3c), item_blk32(d, sel_b),
+                                     d.npw, d.work32, blockIdx.x, blockIdx.y, zs);
 }
 
 template <int MODE>
 __global__ void kb_splitk_reduce32(const ItemDev* __restrict__ D, double alpha, int coef_step) {
   const ItemDev& d = D[blockIdx.y];
   if (d.nproj <= 0) return;
-  const SplitPlan p = split_plan32<MODE>(d.nproj, d.nb, d.npw, d.gemm_target);
+  const SplitPlan p = split_plan32(d.nproj, d.nb, d.npw, d.gemm_target);
   const double* alpha_dev = coef_step >= 0 ? d.coef + 3 * coef_step : nullptr;
   splitk_reduce32_body(d.nproj, d.nb, (int)p.nsplit, d.work32, alpha, alpha_dev, d.ekb, d.cprj32,
                        d.nproj, reinterpret_cast<__bf16*>(d.cprj3), blockIdx.x);
@@ -985,35 +1075,43 @@ kb_gemm_nn32(const ItemDev* __restrict__ D, int sel_c) {
 
 }  // namespace
 
-size_t gemm_cn32_work_elems(int64_t m, int64_t n, int64_t k, int bf16) {
-  // the largest target a caller can set, and the default rule's
-  const SplitPlan p = bf16 ? split_plan32<MODE_BF16>(m, n, k, kTargetBlocks - 1)
-                           : split_plan32<MODE_F32>(m, n, k, kTargetBlocks - 1);
-  const SplitPlan q = bf16 ? split_plan32<MODE_BF16>(m, n, k, 0) : split_plan32<MODE_F32>(m, n, k, 0);
-  return (size_t)(std::max(p.nsplit, q.nsplit) * m * n);
+size_t gemm_cn32_work_elems(int64_t m, int64_t n, int64_t k) {
+  const SplitPlan p = split_plan32(m, n, k, kTargetBlocks);
+  const WidePlan w = split_plan32_wide(m, n, k, kTargetBlocks);
+  return (size_t)(std::max(p.nsplit, 2 * (w.per > 1 ? w.p.nsplit : 0)) * m * n);   // FP64 partials: two elements
 }
+
+namespace {
+template <class W>
+hipError_t splitk_reduce32(int64_t m, int64_t n, int64_t nsplit, const W* work, double alpha,
+                           const double* alpha_dev, const double* rowscale, float2* C, int64_t ldc,
+                           uint16_t* c3, hipStream_t s) {
+  const unsigned blocks = splitk_blocks(m * n, splitk_parts((int)nsplit));
+  hipLaunchKernelGGL(k_splitk_reduce32<W>, dim3(blocks), dim3(256), 0, s, m, n, (int)nsplit, work, alpha,
+                     alpha_dev, rowscale, C, ldc, reinterpret_cast<__bf16*>(c3));
+  return hipGetLastError();
+}
+dim3 split_grid(const SplitPlan& p) {
+  return dim3((unsigned)(kXcds * p.tiles_m * p.tiles_n * ((p.nsplit + kXcds - 1) / kXcds)));
+}
+}  // namespace
 
 hipError_t launch_gemm_cn32(int bf16, int64_t m, int64_t n, int64_t k, double alpha, const float2* A,
                             int64_t lda, const float2* B, int64_t ldb, float2* C, int64_t ldc,
                             const double* rowscale, float2* work, hipStream_t s,
                             const double* alpha_dev, int target) {
   if (m <= 0 || n <= 0) return hipSuccess;
-  const SplitPlan p = bf16 ? split_plan32<MODE_BF16>(m, n, k, target)
-                           : split_plan32<MODE_F32>(m, n, k, target);
-  const dim3 grid((unsigned)(kXcds * p.tiles_m * p.tiles_n * ((p.nsplit + kXcds - 1) / kXcds)));
+  const SplitPlan p = split_plan32(m, n, k, target);
   if (bf16)
-    hipLaunchKernelGGL(k_gemm_cn32<MODE_BF16>, grid, dim3(kThreads), 0, s, m, n, k, p.ksplit, A, lda,
-                       B, ldb, work, (int)p.tiles_m, (int)p.tiles_n, (int)p.nsplit);
+    hipLaunchKernelGGL(k_gemm_cn32<MODE_BF16>, split_grid(p), dim3(kThreads), 0, s, m, n, k, p.ksplit, A,
+                       lda, B, ldb, work, (int)p.tiles_m, (int)p.tiles_n, (int)p.nsplit);
   else
-    hipLaunchKernelGGL(k_gemm_cn32<MODE_F32>, grid, dim3(kThreads), 0, s, m, n, k, p.ksplit, A, lda,
-                       B, ldb, work, (int)p.tiles_m, (int)p.tiles_n, (int)p.nsplit);
+    hipLaunchKernelGGL(k_gemm_cn32<MODE_F32>, split_grid(p), dim3(kThreads), 0, s, m, n, k, p.ksplit, A,
+                       lda, B, ldb, work, (int)p.tiles_m, (int)p.tiles_n, (int)p.nsplit);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t tot = m * n;
-  hipLaunchKernelGGL(k_splitk_reduce32, dim3(splitk_blocks(tot, splitk_parts((int)p.nsplit))), dim3(256), 0, s, m, n,
-                     (int)p.nsplit, (const float2*)work, alpha, alpha_dev, rowscale, C, ldc,
-                     (__bf16*)nullptr);
-  return hipGetLastError();
+  return splitk_reduce32(m, n, p.nsplit, (const float2*)work, alpha, alpha_dev, rowscale, C, ldc,
+                         nullptr, s);
 }
 
 hipError_t launch_gemm_cn32_s3(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3,
@@ -1021,18 +1119,22 @@ hipError_t launch_gemm_cn32_s3(int64_t m, int64_t n, int64_t k, double alpha, co
                                const double* rowscale, float2* work, hipStream_t s,
                                const double* alpha_dev, int target, uint16_t* c3) {
   if (m <= 0 || n <= 0) return hipSuccess;
-  const SplitPlan p = split_plan32<MODE_F32>(m, n, k, target);
-  const dim3 grid((unsigned)(kXcds * p.tiles_m * p.tiles_n * ((p.nsplit + kXcds - 1) / kXcds)));
-  hipLaunchKernelGGL(k_gemm_cn32_s3, grid, dim3(kThreads), 0, s, m, n, k, p.ksplit,
-                     reinterpret_cast<const __bf16*>(a3), B, ldb, work, (int)p.tiles_m,
-                     (int)p.tiles_n, (int)p.nsplit);
+  const WidePlan w = split_plan32_wide(m, n, k, target);
+  const SplitPlan& p = w.p;
+  const __bf16* a = reinterpret_cast<const __bf16*>(a3);
+  double2* work64 = reinterpret_cast<double2*>(work);
+  if (w.per > 1)
+    hipLaunchKernelGGL(k_gemm_cn32_s3<true>, split_grid(p), dim3(kThreads), 0, s, m, n, k, p.ksplit,
+                       w.sub, a, B, ldb, work64, (int)p.tiles_m, (int)p.tiles_n, (int)p.nsplit);
+  else
+    hipLaunchKernelGGL(k_gemm_cn32_s3<false>, split_grid(p), dim3(kThreads), 0, s, m, n, k, p.ksplit,
+                       w.sub, a, B, ldb, work, (int)p.tiles_m, (int)p.tiles_n, (int)p.nsplit);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t tot = m * n;
-  hipLaunchKernelGGL(k_splitk_reduce32, dim3(splitk_blocks(tot, splitk_parts((int)p.nsplit))), dim3(256), 0, s, m, n,
-                     (int)p.nsplit, (const float2*)work, alpha, alpha_dev, rowscale, C, ldc,
-                     reinterpret_cast<__bf16*>(c3));
-  return hipGetLastError();
+  if (w.per > 1)
+    return splitk_reduce32(m, n, p.nsplit, (const double2*)work64, alpha, alpha_dev, rowscale, C, ldc,
+                           c3, s);
+  return splitk_reduce32(m, n, p.nsplit, (const float2*)work, alpha, alpha_dev, rowscale, C, ldc, c3, s);
 }
 
 namespace {
@@ -1041,18 +1143,24 @@ hipError_t gemm_cn32_h1(int64_t m, int64_t n, int64_t k, double alpha, const uin
                         int64_t ldb, float2* C, int64_t ldc, const double* rowscale, float2* work,
                         hipStream_t s, const double* alpha_dev, int target, uint16_t* c3) {
   if (m <= 0 || n <= 0) return hipSuccess;
-  const SplitPlan p = split_plan32<MODE_BF16>(m, n, k, target);
-  const dim3 grid((unsigned)(kXcds * p.tiles_m * p.tiles_n * ((p.nsplit + kXcds - 1) / kXcds)));
-  hipLaunchKernelGGL(k_gemm_cn32_h1<SB>, grid, dim3(kThreads), 0, s, m, n, k, p.ksplit,
-                     reinterpret_cast<const __bf16*>(a3), B, ldb, work, (int)p.tiles_m,
-                     (int)p.tiles_n, (int)p.nsplit);
+  const WidePlan w = split_plan32_wide(m, n, k, target);
+  const SplitPlan& p = w.p;
+  const __bf16* a = reinterpret_cast<const __bf16*>(a3);
+  double2* work64 = reinterpret_cast<double2*>(work);
+  if (w.per > 1)
+    hipLaunchKernelGGL((k_gemm_cn32_h1<SB, true>), split_grid(p), dim3(kThreads), 0, s, m, n, k,
+                       p.ksplit, w.sub, a, B, ldb, work64, (int)p.tiles_m, (int)p.tiles_n,
+                       (int)p.nsplit);
+  else
+    hipLaunchKernelGGL((k_gemm_cn32_h1<SB, false>), split_grid(p), dim3(kThreads), 0, s, m, n, k,
+                       p.ksplit, w.sub, a, B, ldb, work, (int)p.tiles_m, (int)p.tiles_n,
+                       (int)p.nsplit);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t tot = m * n;
-  hipLaunchKernelGGL(k_splitk_reduce32, dim3(splitk_blocks(tot, splitk_parts((int)p.nsplit))), dim3(256), 0, s, m, n,
-                     (int)p.nsplit, (const float2*)work, alpha, alpha_dev, rowscale, C, ldc,
-                     reinterpret_cast<__bf16*>(c3));
-  return hipGetLastError();
+  if (w.per > 1)
+    return splitk_reduce32(m, n, p.nsplit, (const double2*)work64, alpha, alpha_dev, rowscale, C, ldc,
+                           c3, s);
+  return splitk_reduce32(m, n, p.nsplit, (const float2*)work, alpha, alpha_dev, rowscale, C, ldc, c3, s);
 }
 
 template <class SC>
@@ -1109,8 +1217,8 @@ hipError_t launch_gemm_nn32_s3(int64_t m, int64_t n, int64_t k, double alpha, co
 }
 
 int fused_cn32_nsplit(int bf16, int64_t npw, int64_t nb, int64_t nproj, int target) {
-  const SplitPlan p = bf16 ? split_plan32<MODE_BF16>(nproj, nb, npw, target)
-                           : split_plan32<MODE_F32>(nproj, nb, npw, target);
+  const SplitPlan p = bf16 ? split_plan32(nproj, nb, npw, target)
+                           : split_plan32(nproj, nb, npw, target);
   return (int)p.nsplit;
 }
 

@@ -407,7 +407,6 @@ struct SplitPlan {
 // 85, 68 - 69, 79.  With more tiles few splits do anyway (864 x 512 over
 // 124289: 6.6 ms at 2048, 10.5 at 1024).  Fused and per-item launches share
 // the rule, and never exceed the workspace sized for kTargetBlocks.
-constexpr int kFewTiles = 32, kFewTilesTarget = 512;
 __host__ __device__ inline int split_target(int target, int64_t tiles) {
   if (target >= 1 && target <= kTargetBlocks) return target;
   return tiles <= kFewTiles ? kFewTilesTarget : kTargetBlocks;

@@ -1276,11 +1276,10 @@ pw_status pw_ham_create(pw_ctx* ctx, const pw_ham_desc* d, pw_ham** out) {
     {
       // split-K partials of the FP32 / BF16 projections and Gram matrices
       size_t w32 = 1;
-      for (int64_t nb = 1; nb <= h->nb_max; ++nb)
-        for (int bf = 0; bf < 2; ++bf) {
-          if (h->nproj > 0) w32 = std::max(w32, gemm_cn32_work_elems(h->nproj, nb, npw, bf));
-          w32 = std::max(w32, gemm_cn32_work_elems(nb, nb, npw, bf));
-        }
+      for (int64_t nb = 1; nb <= h->nb_max; ++nb) {
+        if (h->nproj > 0) w32 = std::max(w32, gemm_cn32_work_elems(h->nproj, nb, npw));
+        w32 = std::max(w32, gemm_cn32_work_elems(nb, nb, npw));
+      }
       TRY(dalloc(h, &h->work32, w32));
       TRY(dalloc(h, &h->gram32, (size_t)(h->nb_max * h->nb_max)));
     }

@@ -351,6 +351,10 @@ hipError_t launch_gemm_nn(int64_t m, int64_t n, int64_t k, double alpha, const c
 // the eighth digit from those of a saved run.
 constexpr int64_t kReproBands = 64;
 
+// Split products of up to kFewTiles output tiles aim at kFewTilesTarget workgroups
+// (two per CU) by default: figures at the plans in gemm_kernels.hip, gemm32_kernels.hip.
+constexpr int kFewTiles = 32, kFewTilesTarget = 512;
+
 // Split-K reductions: a workgroup of splitk_threads(zp) threads takes zp threads
 // to an element (thread part q takes the splits q, q + zp, ..., in
 // order, then the parts are added in order).  zp = 1, for more than kReproBands
@@ -442,7 +446,7 @@ hipError_t launch_fused_col_fwd_nl(const FusedFft& f, const ItemDev* D, int sel_
 
 // Low-precision products (gemm32_kernels.hip): complex64 operands, FP32
 // accumulation; bf16 != 0 rounds the MFMA operands to bfloat16.
-size_t gemm_cn32_work_elems(int64_t m, int64_t n, int64_t k, int bf16);
+size_t gemm_cn32_work_elems(int64_t m, int64_t n, int64_t k);
 hipError_t launch_gemm_cn32(int bf16, int64_t m, int64_t n, int64_t k, double alpha, const float2* A,
                             int64_t lda, const float2* B, int64_t ldb, float2* C, int64_t ldc,
                             const double* rowscale, float2* work, hipStream_t s,
