@@ -372,9 +372,13 @@ pw_status pw_upper_bound(pw_ham* ham, double* b_host);
 /* ---------------------------------------------------------------------------
  * Launch-shape tuning of H*psi.  A handle starts with the register-resident
  * FFT kernels where they exist, the largest band chunk its buffer holds and
- * 4096 target blocks for the split-K projector product (the FP64 product
- * uses at most 2048); pw_ham_autotune
- * times alternatives on the device and keeps the fastest.
+ * 4096 target blocks for the split-K projector product; pw_ham_autotune
+ * times alternatives on the device and keeps the fastest.  4096 is the
+ * library's own choice: FP64 aims at 512 blocks for results of up to 32 tiles
+ * of 64 x 64 and at 2048 for more; FP32 and BF16 split the contraction for
+ * 4096, and for up to 32 tiles a block may form several of those splits and
+ * add them in FP64 (the same sums).  Any other value is taken as it is, by
+ * FP64 up to 2048.
  * ------------------------------------------------------------------------- */
 typedef struct {
   int32_t reg_col;        /* 1: register-resident column kernels (N3 in the fast set)       */
@@ -384,7 +388,8 @@ typedef struct {
   int32_t plane_variant32;/* FP32 plane kernel: 0, 1 as above (1 also for 120, 128, 144, 160);
                              2 transforms exchanged through LDS (N1 = N2 = 144)            */
   int32_t chunk;          /* bands per FFT launch, [1, the handle's buffer]                  */
-  int32_t gemm_blocks;    /* split-K target block count of P^H psi, [1, 4096] (FP64: <= 2048) */
+  int32_t gemm_blocks;    /* split-K target block count of P^H psi, [1, 4096] (FP64: 2049 to
+                             4095 act as 2048; 4096 see above)                             */
   int32_t nn_tile;        /* tall FP64 products P C, Y Q, Y U^-1: 0 64x64, 1 128x64 tiles    */
   int32_t nn_tile32;      /* the same choice for the BF16 product P C                        */
   double ms;              /* pw_ham_autotune: median time of one H*psi of nb bands           */

@@ -398,17 +398,18 @@ struct SplitPlan {
   int64_t tiles_m, tiles_n, nsplit, ksplit;
 };
 
-// Workgroups a split product aims at: the caller's target, or by the output's
-// tiles where that is outside [1, kTargetBlocks] (the default; the FP32
-// products accept more).  Up to 32 tiles the partials, written and read once
-// per split, cost more than filling the chip beyond two workgroups per CU
-// gains: 256 x 160 outputs over 37073 values 259 us at 2048 workgroups, 237 -
-// 249 at 768 - 512, 303 at 384 (one and a half per CU); 192 x 117 over 16346
-// 85, 68 - 69, 79.  With more tiles few splits do anyway (864 x 512 over
-// 124289: 6.6 ms at 2048, 10.5 at 1024).  Fused and per-item launches share
-// the rule, and never exceed the workspace sized for kTargetBlocks.
+// Workgroups a split product aims at: the caller's target, at most kTargetBlocks,
+// or by the output's tiles at the default (below 1, or kTargetDefault).  Up to
+// kFewTiles tiles the partials, written and read once per split, cost more than
+// filling the chip beyond two workgroups per CU gains: 256 x 160 outputs over
+// 37073 values 259 us at 2048 workgroups, 237 - 249 at 768 - 512, 303 at 384 (one
+// and a half per CU); 192 x 117 over 16346 85, 68 - 69, 79.  With more tiles few
+// splits do anyway (864 x 512 over 124289: 6.6 ms at 2048, 10.5 at 1024).  Fused
+// and per-item launches share the rule, and never exceed the workspace sized for
+// kTargetBlocks.
+constexpr int kTargetDefault = 4096;   // the handles' gemm_blocks to start with
 __host__ __device__ inline int split_target(int target, int64_t tiles) {
-  if (target >= 1 && target <= kTargetBlocks) return target;
+  if (target >= 1 && target < kTargetDefault) return target < kTargetBlocks ? target : kTargetBlocks;
   return tiles <= kFewTiles ? kFewTilesTarget : kTargetBlocks;
 }
 
