@@ -848,13 +848,13 @@ k_gemm_nn32_h1(int64_t M, int64_t N, int64_t K, float alpha, const __bf16* __res
   gemm_nn32_h1_body<TM, SC>(M, N, K, alpha, A3, B3, beta, C, ldc, bx, by);
 }
 
-// The stored three-term copy X3 of a complex64 matrix X (R rows, contraction
+// The stored three-term copy X3 of a matrix X rounded to FP32 (R rows, contraction
 // K; element (r, k) at X[r sr + k sk]), all s3_rows(R) x 32 nst entries
 // written (zero padding included).  A workgroup per 64-row panel and K chunk
 // (grid-strided over the chunks), through LDS: reads run along whichever
 // index is contiguous in X, writes along K within the chunks.
 __global__ void __launch_bounds__(256)
-k_split3_s3(int64_t R, int64_t K, const float2* __restrict__ X, int64_t sr, int64_t sk,
+k_split3_s3(int64_t R, int64_t K, const cplx* __restrict__ X, int64_t sr, int64_t sk,
             __bf16* __restrict__ X3) {
   __shared__ float2 t[64][33];
   const int64_t r0 = (int64_t)blockIdx.x * 64;
@@ -865,7 +865,12 @@ k_split3_s3(int64_t R, int64_t K, const float2* __restrict__ X, int64_t sr, int6
       const int rr = sr == 1 ? (e & 63) : (e >> 5);
       const int kk = sr == 1 ? (e >> 6) : (e & 31);
       const int64_t r = r0 + rr, k = k0 + kk;
-      t[rr][kk] = (r < R && k < K) ? X[r * sr + k * sk] : make_float2(0.f, 0.f);
+      float2 v = make_float2(0.f, 0.f);
+      if (r < R && k < K) {
+        const cplx x = X[r * sr + k * sk];
+        v = make_float2((float)x.x, (float)x.y);
+      }
+      t[rr][kk] = v;
     }
     __syncthreads();
     for (int e = threadIdx.x; e < 64 * 32; e += 256) {
@@ -1254,7 +1259,7 @@ hipError_t launch_fused_gemm_nn32(int bf16, int nitems, int64_t m_max, int64_t n
 
 size_t split3_elems(int64_t rows, int64_t k) { return (size_t)(s3_rows(rows) * s3_nst(k) * kS3Chunk); }
 
-hipError_t launch_split3(int64_t rows, int64_t k, const float2* X, int64_t sr, int64_t sk,
+hipError_t launch_split3(int64_t rows, int64_t k, const cplx* X, int64_t sr, int64_t sk,
                          uint16_t* X3, hipStream_t s) {
   if (rows <= 0 || k <= 0) return hipSuccess;
   const dim3 grid((unsigned)(s3_rows(rows) / 64), (unsigned)std::min<int64_t>(s3_nst(k), 65535));

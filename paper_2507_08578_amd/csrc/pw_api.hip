@@ -1259,12 +1259,10 @@ pw_status pw_ham_create(pw_ctx* ctx, const pw_ham_desc* d, pw_ham** out) {
     HIPCHK(ctx, launch_real_to_f32(npw, h->kin, 1.0, h->kin32, s));
     HIPCHK(ctx, launch_real_to_f32(nbox, h->vscaled, 1.0, h->vs32, s));
     if (h->nproj > 0) {
-      TRY(dalloc(h, &h->proj32, (size_t)(npw * h->nproj)));
-      HIPCHK(ctx, launch_block_to_f32(npw, h->nproj, h->proj, npw, h->proj32, npw, s));
       TRY(dalloc(h, &h->proj3, split3_elems(npw, h->nproj)));
-      HIPCHK(ctx, launch_split3(npw, h->nproj, h->proj32, 1, npw, h->proj3, s));
+      HIPCHK(ctx, launch_split3(npw, h->nproj, h->proj, 1, npw, h->proj3, s));
       TRY(dalloc(h, &h->proj3c, split3_elems(h->nproj, npw)));
-      HIPCHK(ctx, launch_split3(h->nproj, npw, h->proj32, npw, 1, h->proj3c, s));
+      HIPCHK(ctx, launch_split3(h->nproj, npw, h->proj, npw, 1, h->proj3c, s));
       TRY(dalloc(h, &h->cprj32, (size_t)(h->nproj * h->nb_max)));
       // the reduction writes the entries of the nb bands it forms: the
       // projector padding stays zero, and rows of bands past a call's nb

@@ -125,9 +125,8 @@ struct pw_ham {
   bool low_prec = false;
   float* kin32 = nullptr;
   float* vs32 = nullptr;
-  float2* proj32 = nullptr;
-  // proj32 split into three bf16 terms (launch_split3 layout) for the FP32 and
-  // bf16 products: rows = plane waves (P C) and rows = projectors (P^H psi)
+  // proj rounded to FP32 and split into three bf16 terms (launch_split3 layout) for
+  // the FP32 and bf16 products: rows = plane waves (P C) and rows = projectors (P^H psi)
   uint16_t* proj3 = nullptr;
   uint16_t* proj3c = nullptr;
   uint16_t* cprj3 = nullptr;   // cprj32^T in three terms (rows = bands), written by P^H psi

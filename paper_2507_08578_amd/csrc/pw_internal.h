@@ -478,13 +478,13 @@ hipError_t launch_gemm_nn32_h1(int64_t m, int64_t n, int64_t k, double alpha, co
 hipError_t launch_gemm_nn32_s16(int64_t m, int64_t n, int64_t k, double alpha, const uint16_t* a3,
                                 const uint16_t* b3, double beta, bf16c* C, int64_t ldc, hipStream_t s,
                                 int tile);
-// Stored three-term copies: X3 holds X (rows x k; element (r, c) at
+// Stored three-term copies: X3 holds X rounded to FP32 (rows x k; element (r, c) at
 // X[r sr + c sk]) split exactly into three bf16 terms per real part, in
 // chunks of 32 contraction values (six planes of 32 bf16 per chunk, a row's
 // chunks consecutive), rows padded to a multiple of 64 and k to 32, with
 // zeros; split3_elems gives its size in bf16.
 size_t split3_elems(int64_t rows, int64_t k);
-hipError_t launch_split3(int64_t rows, int64_t k, const float2* X, int64_t sr, int64_t sk,
+hipError_t launch_split3(int64_t rows, int64_t k, const cplx* X, int64_t sr, int64_t sk,
                          uint16_t* X3, hipStream_t s);
 
 // Precision conversions
