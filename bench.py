@@ -90,24 +90,6 @@ COUNTER_FILES = {
 }
 
 
-TWO_FACTOR = {16, 18, 20, 24, 25, 27, 30, 32, 36, 40, 45, 48, 50, 54, 60, 64, 72, 75, 80, 81, 90, 96,
-              100, 108, 120, 128, 135, 144, 150, 160}
-
-
-def plane_kernel(ham, prec):
-    """Name of the plane kernel that the handle's tuning and the library's rule
-    on the box select for this precision."""
-    t, (n1, n2, _) = ham.get_tuning(), ham.box
-    lp = prec != "fp64"
-    variant = t["plane_variant32" if lp else "plane_variant"]
-    if lp and t["reg_plane"] and variant == 2:
-        return "k_plane_ls"
-    wins = n1 >= 36 and n1 not in (128, 160) if lp else n1 in (36, 72)
-    if t["reg_plane"] and not (variant == 0 and wins):
-        return "k_plane_reg"
-    return "k_plane_pq" if {n1, n2} <= TWO_FACTOR else "k_plane"
-
-
 def measured_traffic(config, prec, stage, kernel, bands_per_launch):
     """HBM bytes per launch from the committed FETCH_SIZE / WRITE_SIZE summary,
     or None when there is none or the kernel sources changed since it was taken."""
@@ -207,7 +189,7 @@ def roofline(stages, steps, w, ham, nb, prec, config=None):
         fl = per_band * bands_per_launch
         peak = PEAK["fp64_valu" if prec == "fp64" else "fp32_valu"]
         ach = fl / (avg_ms * 1e-3) / 1e12
-        kname = plane_kernel(ham, prec)
+        kname = ham.plane_kernel(prec)
         extra = {}
         if prec != "fp64":
             # 157.3 counts packed FP32 (two FMAs per lane and instruction); the

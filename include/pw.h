@@ -396,6 +396,10 @@ typedef struct {
 } pw_tuning;
 
 pw_status pw_ham_get_tuning(const pw_ham* ham, pw_tuning* t);
+/* Name of the plane kernel that H psi runs at the current tuning in precision
+ * prec, as a profiler shows it (k_plane, k_plane_reg, k_plane_ls, k_plane_pq);
+ * NULL for a bad argument. */
+const char* pw_ham_plane_kernel(const pw_ham* ham, pw_prec prec);
 /* UNSUPPORTED for a kernel family the box has no kernel for. */
 pw_status pw_ham_set_tuning(pw_ham* ham, const pw_tuning* t);
 /*

@@ -431,6 +431,10 @@ class Hamiltonian:
             setattr(t, k, cur[k])
         self.ctx.check(_LIB.pw_ham_set_tuning(self.handle, ctypes.byref(t)))
 
+    def plane_kernel(self, prec="fp64") -> str:
+        """Name of the plane kernel that H psi runs at the current tuning."""
+        return _LIB.pw_ham_plane_kernel(self.handle, _prec(prec)).decode()
+
     def tuning_key(self, prec, nb: int) -> str:
         """Shape key of the tuning cache (as pw_autotune writes it): box, sphere
         columns and extent, npw, nproj, nb, precision code."""

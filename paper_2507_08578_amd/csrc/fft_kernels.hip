@@ -522,18 +522,20 @@ hipError_t launch_fft_col_inv32(const BoxPlan& p, const FftLaunchCfg& cfg, int n
 
 hipError_t launch_fft_plane(const BoxPlan& p, const FftLaunchCfg& cfg, int nb, const double* vscaled,
                             cplx* T, hipStream_t s) {
-  if (cfg.reg_plane && !(cfg.plane_variant == 0 && cfg.pq64_sq))
-    return launch_fft_plane_reg(p, cfg.plane_variant, nb, vscaled, T, s);
-  if (cfg.pq64) return launch_fft_plane_pq(p, nb, vscaled, T, s);
-  return plane_generic<double2>(p, cfg, nb, vscaled, T, s);
+  switch (fft_plane_kernel(cfg, false)) {
+    case PlaneKernel::Reg: return launch_fft_plane_reg(p, cfg.plane_variant, nb, vscaled, T, s);
+    case PlaneKernel::Pq: return launch_fft_plane_pq(p, nb, vscaled, T, s);
+    default: return plane_generic<double2>(p, cfg, nb, vscaled, T, s);
+  }
 }
 hipError_t launch_fft_plane32(const BoxPlan& p, const FftLaunchCfg& cfg, int nb, const float* vscaled,
                               float2* T, hipStream_t s) {
-  if (cfg.reg_plane && cfg.plane_variant32 == 2) return launch_fft_plane_ls32(p, nb, vscaled, T, s);
-  if (cfg.reg_plane && !(cfg.plane_variant32 == 0 && cfg.pq32_sq))
-    return launch_fft_plane_reg32(p, cfg.plane_variant32, nb, vscaled, T, s);
-  if (cfg.pq32) return launch_fft_plane_pq32(p, nb, vscaled, T, s);
-  return plane_generic<float2>(p, cfg, nb, vscaled, T, s);
+  switch (fft_plane_kernel(cfg, true)) {
+    case PlaneKernel::Ls: return launch_fft_plane_ls32(p, nb, vscaled, T, s);
+    case PlaneKernel::Reg: return launch_fft_plane_reg32(p, cfg.plane_variant32, nb, vscaled, T, s);
+    case PlaneKernel::Pq: return launch_fft_plane_pq32(p, nb, vscaled, T, s);
+    default: return plane_generic<float2>(p, cfg, nb, vscaled, T, s);
+  }
 }
 
 hipError_t launch_fft_col_fwd(const BoxPlan& p, const FftLaunchCfg& cfg, int nb, const cplx* T,

@@ -1626,6 +1626,16 @@ pw_status pw_ham_get_tuning(const pw_ham* h, pw_tuning* t) {
   return PW_OK;
 }
 
+const char* pw_ham_plane_kernel(const pw_ham* h, pw_prec prec) {
+  if (!h || prec < PW_FP64 || prec > PW_BF16) return nullptr;
+  switch (fft_plane_kernel(h->cfg, prec != PW_FP64)) {
+    case PlaneKernel::Reg: return "k_plane_reg";
+    case PlaneKernel::Ls: return "k_plane_ls";
+    case PlaneKernel::Pq: return "k_plane_pq";
+    default: return "k_plane";
+  }
+}
+
 pw_status pw_ham_set_tuning(pw_ham* h, const pw_tuning* t) {
   if (!h || !t) return fail(nullptr, PW_ERR_INVALID_ARG, "ham or tuning is NULL");
   if ((t->reg_col != 0 && t->reg_col != 1) || (t->reg_plane != 0 && t->reg_plane != 1) ||

@@ -176,6 +176,16 @@ struct FftLaunchCfg {
   int plane_variant;        // FP64 register plane kernel: 0 = lane groups <= 16, 1 = <= 8
   int plane_variant32;      // FP32: 0 / 1 as above, 2 = LDS-exchange kernel (fft_ls.hip)
 };
+// The plane kernel that a configuration selects: the two-factor one in place of
+// the register kernel's variant 0 where it is the faster, and in place of the
+// general one wherever it holds the box.
+enum class PlaneKernel { General, Reg, Ls, Pq };
+inline PlaneKernel fft_plane_kernel(const FftLaunchCfg& c, bool fp32) {
+  const int variant = fp32 ? c.plane_variant32 : c.plane_variant;
+  if (c.reg_plane && fp32 && variant == 2) return PlaneKernel::Ls;
+  if (c.reg_plane && !(variant == 0 && (fp32 ? c.pq32_sq : c.pq64_sq))) return PlaneKernel::Reg;
+  return (fp32 ? c.pq32 : c.pq64) ? PlaneKernel::Pq : PlaneKernel::General;
+}
 
 // Host-side choice of tiles and LDS sizes; returns false if this GPU's LDS
 // cannot hold the plane kernel's working set.
