@@ -374,11 +374,11 @@ pw_status pw_upper_bound(pw_ham* ham, double* b_host);
  * FFT kernels where they exist, the largest band chunk its buffer holds and
  * 4096 target blocks for the split-K projector product; pw_ham_autotune
  * times alternatives on the device and keeps the fastest.  4096 is the
- * library's own choice: FP64 aims at 512 blocks for results of up to 32 tiles
- * of 64 x 64 and at 2048 for more; FP32 and BF16 split the contraction for
- * 4096, and for up to 32 tiles a block may form several of those splits and
- * add them in FP64 (the same sums).  Any other value is taken as it is, by
- * FP64 up to 2048.
+ * library's own choice: FP64 aims at 512 or 768 blocks for results of few
+ * 64 x 64 tiles over short contractions and at 2048 otherwise; FP32 and BF16 split the
+ * contraction for 4096, and in the same cases a block may form several of
+ * those splits and add them in FP64 (the same sums).  Any other value is taken
+ * as it is, by FP64 up to 2048.
  * ------------------------------------------------------------------------- */
 typedef struct {
   int32_t reg_col;        /* 1: register-resident column kernels (N3 in the fast set)       */

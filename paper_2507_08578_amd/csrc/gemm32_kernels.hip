@@ -1008,26 +1008,35 @@ __host__ __device__ inline SplitPlan split_plan32(int64_t m, int64_t n, int64_t 
   return p;
 }
 
-// At the default target, outputs of few tiles: one workgroup takes `per` of those
-// splits, which it adds up in FP64 (WideSum), so the sums are what they are above
-// while fewer partials are written and read (kFewTilesTarget workgroups).  H psi
-// at 256 x 160 outputs over 37073 values, bf16: 665 -> 624 us (product 54 -> 42), at
-// 192 x 117 over 16346, FP32: 206 -> 196 us.  FP32 sums over the whole of a
-// workgroup's range would take 611 and 190 us, but their errors are up to 2.4
-// times as large (37073 values, 12 tiles: 1.0e-7 instead of 4.2e-8).
+// At the default target, for few output tiles over short contractions: one workgroup
+// takes `per` of those splits, which it adds up in FP64 (WideSum), so the sums are
+// what they are above while fewer partials are written and read (at most two
+// workgroups per CU).  Product and reduction, us: one split per workgroup / several:
+//   FP32  15053 x 12, 16, 32 tiles  58 52, 83 63, 132 106    36065 x 4, 8, 16, 24, 28  62 53, 112 80, 149 128, 192 199, 214 192
+//         67773 x 8, 15, 18         162 132, 217 216, 248 261   135421 x 4, 8, 12       171 131, 255 230, 298 334
+//   bf16  36065 x 4, 8, 16, 32      39 33, 75 43, 95 61, 127 91   67773 x 16, 24        121 92, 148 152
+//         135421 x 8, 15, 20        137 104, 173 161, 198 209
+// (more than 32 tiles: 131 194 for 40 over 36065).  FP32 sums over all a workgroup
+// reads would save some more (36065 x 8: 71 and 35), but their errors are up to 2.4
+// times as large (37073 values, 12 tiles: 1.0e-7 instead of 4.2e-8).  Two splits at
+// a time leave too few workgroups (bf16 17168 x 3: 12.4 instead of 10.2).
+constexpr int kWideTarget = 512;
 struct WidePlan {
   SplitPlan p;
   int64_t sub, per;
 };
-inline WidePlan split_plan32_wide(int64_t m, int64_t n, int64_t k, int target) {
+inline WidePlan split_plan32_wide(int mode, int64_t m, int64_t n, int64_t k, int target) {
   WidePlan w{split_plan32(m, n, k, target), 0, 1};
   SplitPlan& p = w.p;
   w.sub = p.ksplit;
   const int64_t tiles = p.tiles_m * p.tiles_n;
-  if ((target >= 1 && target < kTargetBlocks) || tiles > kFewTiles) return w;
-  int64_t want = (kFewTilesTarget + tiles - 1) / tiles;
+  const int64_t most = mode == MODE_BF16 ? 1 << 21 : 1 << 20;
+  if ((target >= 1 && target < kTargetBlocks) || tiles > 32 || k * tiles >= most) return w;
+  int64_t want = kWideTarget / tiles;
   if (want >= 2 * kXcds) want -= want % kXcds;
-  w.per = (p.nsplit + want - 1) / want;
+  const int64_t per = (p.nsplit + want - 1) / want;
+  if (per < 3) return w;
+  w.per = per;
   p.ksplit *= w.per;
   p.nsplit = (p.nsplit + w.per - 1) / w.per;
   return w;
@@ -1082,8 +1091,12 @@ kb_gemm_nn32(const ItemDev* __restrict__ D, int sel_c) {
 
 size_t gemm_cn32_work_elems(int64_t m, int64_t n, int64_t k) {
   const SplitPlan p = split_plan32(m, n, k, kTargetBlocks);
-  const WidePlan w = split_plan32_wide(m, n, k, kTargetBlocks);
-  return (size_t)(std::max(p.nsplit, 2 * (w.per > 1 ? w.p.nsplit : 0)) * m * n);   // FP64 partials: two elements
+  int64_t most = p.nsplit;
+  for (int mode : {MODE_F32, MODE_BF16}) {
+    const WidePlan w = split_plan32_wide(mode, m, n, k, kTargetBlocks);
+    if (w.per > 1) most = std::max(most, 2 * w.p.nsplit);   // FP64 partials: two elements
+  }
+  return (size_t)(most * m * n);
 }
 
 namespace {
@@ -1124,7 +1137,7 @@ hipError_t launch_gemm_cn32_s3(int64_t m, int64_t n, int64_t k, double alpha, co
                                const double* rowscale, float2* work, hipStream_t s,
                                const double* alpha_dev, int target, uint16_t* c3) {
   if (m <= 0 || n <= 0) return hipSuccess;
-  const WidePlan w = split_plan32_wide(m, n, k, target);
+  const WidePlan w = split_plan32_wide(MODE_F32, m, n, k, target);
   const SplitPlan& p = w.p;
   const __bf16* a = reinterpret_cast<const __bf16*>(a3);
   double2* work64 = reinterpret_cast<double2*>(work);
@@ -1148,7 +1161,7 @@ hipError_t gemm_cn32_h1(int64_t m, int64_t n, int64_t k, double alpha, const uin
                         int64_t ldb, float2* C, int64_t ldc, const double* rowscale, float2* work,
                         hipStream_t s, const double* alpha_dev, int target, uint16_t* c3) {
   if (m <= 0 || n <= 0) return hipSuccess;
-  const WidePlan w = split_plan32_wide(m, n, k, target);
+  const WidePlan w = split_plan32_wide(MODE_BF16, m, n, k, target);
   const SplitPlan& p = w.p;
   const __bf16* a = reinterpret_cast<const __bf16*>(a3);
   double2* work64 = reinterpret_cast<double2*>(work);

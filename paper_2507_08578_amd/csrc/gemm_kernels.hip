@@ -399,18 +399,24 @@ struct SplitPlan {
 };
 
 // Workgroups a split product aims at: the caller's target, at most kTargetBlocks,
-// or by the output's tiles at the default (below 1, or kTargetDefault).  Up to
-// kFewTiles tiles the partials, written and read once per split, cost more than
-// filling the chip beyond two workgroups per CU gains: 256 x 160 outputs over
-// 37073 values 259 us at 2048 workgroups, 237 - 249 at 768 - 512, 303 at 384 (one
-// and a half per CU); 192 x 117 over 16346 85, 68 - 69, 79.  With more tiles few
-// splits do anyway (864 x 512 over 124289: 6.6 ms at 2048, 10.5 at 1024).  Fused
-// and per-item launches share the rule, and never exceed the workspace sized for
-// kTargetBlocks.
+// or by the product's size at the default (below 1, or kTargetDefault).  For few
+// output tiles over a contraction k whose splits would be short, the partials,
+// written and read once per split, cost more than filling the chip beyond a few
+// workgroups per CU gains.  Product and reduction, us at 512 / 768 / 2048:
+//     k     tiles
+//    9537   3: 35 39 39     4: 41 45 48       8: 64 66 77      12: 82 81 94     16: 99 102 119
+//   36065   1: 41 45 56     4: 101 101 128    8: 179 171 195   12: 263 242 258  16: 324 309 332
+//  135421   4: 316 303 323  8: 597 566 589   12: 912 855 868   13: 1330 956 941
+//   36065  17: 405 364 351  25: 594 584 510  64: 1211 1591 1195
+// so two per CU for the shortest (not 13 tiles, 112 88 110 at 9537: one workgroup
+// too many for two), three while a CU's last workgroups are not yet long, and
+// 2048 beyond.  Fused and per-item launches share the rule, and never exceed the
+// workspace sized for kTargetBlocks.
 constexpr int kTargetDefault = 4096;   // the handles' gemm_blocks to start with
-__host__ __device__ inline int split_target(int target, int64_t tiles) {
+__host__ __device__ inline int split_target(int target, int64_t tiles, int64_t k) {
   if (target >= 1 && target < kTargetDefault) return target < kTargetBlocks ? target : kTargetBlocks;
-  return tiles <= kFewTiles ? kFewTilesTarget : kTargetBlocks;
+  if (tiles > 16 || k * tiles >= (1 << 20)) return kTargetBlocks;
+  return tiles <= 12 && k * tiles < (3 << 15) ? 512 : 768;
 }
 
 __host__ __device__ inline SplitPlan split_plan(int64_t m, int64_t n, int64_t k, int target) {
@@ -418,7 +424,7 @@ __host__ __device__ inline SplitPlan split_plan(int64_t m, int64_t n, int64_t k,
   p.tiles_m = (m + kBM - 1) / kBM;
   p.tiles_n = (n + kBN - 1) / kBN;
   const int64_t tiles = p.tiles_m * p.tiles_n;
-  target = split_target(target, tiles);
+  target = split_target(target, tiles, k);
   int64_t want = (target + tiles - 1) / tiles;
   // at least two K stages per split (short splits keep small products latency-light)
   const int64_t maxs = (k + kKcCN * 2 - 1) / (kKcCN * 2) > 1 ? (k + kKcCN * 2 - 1) / (kKcCN * 2) : 1;
@@ -542,7 +548,7 @@ hipError_t launch_gemm_cn(int64_t m, int64_t n, int64_t k, double alpha, const c
     return hipErrorInvalidValue;
   if (craw && (upper || beta != 0.0 || ldraw < m)) return hipErrorInvalidValue;
   SplitPlan p = split_plan(m, n, k, target);
-  target = split_target(target, p.tiles_m * p.tiles_n);
+  target = split_target(target, p.tiles_m * p.tiles_n, k);
   const int64_t T = (m + kBM - 1) / kBM, nact = T * (T + 1) / 2;
   if (T == 1) upper = 0;   // a single tile: nothing to skip
   // packed splits that fit the workspace (sized for the full product at kTargetBlocks)

@@ -98,7 +98,7 @@ struct pw_ham {
   int64_t chunk = 0;         // bands per FFT launch (tunable, <= chunk_alloc)
   int64_t chunk_alloc = 0;   // bands the FFT work buffer holds
   int gemm_target = 4096;    // split-K target block count of the projector product (tunable;
-                             // FP64: at most 2048, and 4096 by the output's tiles)
+                             // FP64: at most 2048, and 4096 by the product's size)
   int nn_tile = 0;           // workgroup tile of the tall FP64 products P C, Y Q, Y U^-1 (tunable)
   int nn_tile32 = 0;         // the same for the BF16 product P C (tunable)
   bool reg_col_ok = false, reg_plane_ok = false, narrow_ok = false, narrow32_ok = false;

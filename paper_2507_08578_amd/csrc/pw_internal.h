@@ -361,10 +361,6 @@ hipError_t launch_gemm_nn(int64_t m, int64_t n, int64_t k, double alpha, const c
 // the eighth digit from those of a saved run.
 constexpr int64_t kReproBands = 64;
 
-// Split products of up to kFewTiles output tiles aim at kFewTilesTarget workgroups
-// (two per CU) by default: figures at the plans in gemm_kernels.hip, gemm32_kernels.hip.
-constexpr int kFewTiles = 32, kFewTilesTarget = 512;
-
 // Split-K reductions: a workgroup of splitk_threads(zp) threads takes zp threads
 // to an element (thread part q takes the splits q, q + zp, ..., in
 // order, then the parts are added in order).  zp = 1, for more than kReproBands
