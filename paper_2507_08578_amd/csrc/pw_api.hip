@@ -161,8 +161,8 @@ pw_status ham_apply(pw_ham* h, int64_t nb, const cplx* in, int64_t ldin, cplx* o
                     const double* coef, cplx* craw, bool repro) {
   pw_ctx* c = h->ctx;
   hipStream_t s = c->stream;
-  // repro (kReproBands): the split count and the FFT kernels that do not follow
-  // the shape rules
+  // repro (Rayleigh-Ritz above kReproBands bands): the split count and the FFT
+  // kernels that do not follow the rules by shape
   FftLaunchCfg cfg = h->cfg;
   if (repro) cfg.pq64 = cfg.pq64_sq = false;
   const bool few = nonlocal_in_columns(h->nproj, h->npw, nb, cfg.reg_col);
@@ -1738,8 +1738,9 @@ pw_status pw_ham_autotune(pw_ham* h, pw_prec prec, int64_t nb, int32_t reps, pw_
       for (int pv = 0; pv <= (rp ? 2 : 0); ++pv) {
         if ((pv == 1 && !nok) || (pv == 2 && !lsok)) continue;
         // where the two-factor plane kernel serves the box, reg_plane = 0 selects it
-        // for H psi alone and leaves Rayleigh-Ritz (kReproBands) the general kernel:
-        // 96 x 96, 160 bands, a tie in H psi and 13.4 against 12.2 ms an iteration
+        // for H psi alone and leaves Rayleigh-Ritz above kReproBands bands, which asks
+        // for the kernels without the two-factor ones, the general kernel: 96 x 96, 160
+        // bands, a tie in H psi and 13.4 against 12.2 ms an iteration
         if (!rp && h->reg_plane_ok && (lp ? h->cfg.pq32 : h->cfg.pq64)) continue;
         pw_tuning t = cur;
         t.reg_col = rc;

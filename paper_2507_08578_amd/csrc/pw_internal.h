@@ -353,23 +353,29 @@ hipError_t launch_gemm_nn(int64_t m, int64_t n, int64_t k, double alpha, const c
                           const cplx* B, int64_t ldb, double beta, cplx* C, int64_t ldc,
                           hipStream_t s, int tile = 0);
 
-// Rayleigh-Ritz with more than kReproBands bands, and the orthonormalisation
-// before it, keep one fixed order of every sum and one choice of FP64 kernels:
-// the block Jacobi solver returns Ritz vectors whose phases move by 1e7 .. 1e8
-// times a change of the matrix (160 bands: 4e-9 for 1e-16; 64 bands: 1e-12),
-// so any other rounding there would give vectors that differ, by a phase, in
-// the eighth digit from those of a saved run.
-constexpr int64_t kReproBands = 64;
+// pw_orthonormalize and pw_rayleigh_ritz of more than kReproBands bands keep one
+// fixed order of every sum and one choice of FP64 kernels, without the rules by
+// shape of H psi.  The block Jacobi solver returns Ritz vectors whose phases
+// follow the rounding of the matrix: another rounding (1e-16) moves them by 1e-12
+// at 72 bands, 1e-11 at 100, 1e-10 at 112 to 128, 1e-9 at 144 to 160 and up to 2e-7
+// at 240, while vectors and values themselves move by 1e-12.  So from the same block
+// these two calls return what they did in earlier versions, phases included.  It
+// holds for these calls alone: the filter, LOBPCG and RMM-DIIS follow the rules by
+// shape, and the vectors of a whole solve with them.  It costs the general plane
+// kernel for H Y where N1 != N2: both calls together take 1.1 to 1.6 times as long
+// there (112 to 240 bands), which up to 96 bands the phases are not worth (80
+// bands, 80 x 80 x 40: 3.25 -> 2.71 ms).
+constexpr int64_t kReproBands = 96;
 
 // Split-K reductions: a workgroup of splitk_threads(zp) threads takes zp threads
 // to an element (thread part q takes the splits q, q + zp, ..., in
-// order, then the parts are added in order).  zp = 1, for more than kReproBands
-// columns in FP64, adds the splits one after another, 16 loads at a time in
-// flight.  One load after another leaves a small result to latency: 8 x 16
+// order, then the parts are added in order).  zp = 1, for more than 64 columns in
+// FP64, adds the splits one after another, 16 loads at a time in flight: there are
+// elements enough, and Rayleigh-Ritz keeps its order (kReproBands).  One load after another leaves a small result to latency: 8 x 16
 // elements of 38 splits took 6.7 us, 256 x 160 of 168 splits 55 us (2 TB/s).
 __host__ __device__ inline int splitk_parts(int nsplit) { return nsplit > 32 ? 16 : nsplit > 8 ? 8 : 4; }
 __host__ __device__ inline int splitk_parts64(int nsplit, int64_t n) {
-  return n > kReproBands ? 1 : splitk_parts(nsplit);
+  return n > 64 ? 1 : splitk_parts(nsplit);
 }
 inline int splitk_threads(int zp) { return zp == 1 ? 64 : 256; }
 inline unsigned splitk_blocks(int64_t elems, int zp) {
@@ -431,10 +437,10 @@ __device__ __forceinline__ bool splitk_sum(const W* __restrict__ work, int64_t s
 // bands) 31.5 -> 14.7 us; with the projections in a launch of their own 17.3.
 // Each band reads P again, from L2, so the line is where P fits beside the rest
 // there (1 MiB) and the matrix cores' tiles would hold few rows or columns.
-constexpr int64_t kNlMaxProj = 16, kNlMaxEntries = 65536;
+constexpr int64_t kNlMaxProj = 16, kNlMaxEntries = 65536, kNlMaxBands = 64;
 inline bool nonlocal_in_columns(int64_t nproj, int64_t npw, int64_t nb, bool reg_col) {
   return reg_col && nproj > 0 && nproj <= kNlMaxProj && nproj * npw <= kNlMaxEntries &&
-         nb <= kReproBands;
+         nb <= kNlMaxBands;
 }
 hipError_t launch_fft_col_inv_proj(const BoxPlan& p, int nb, const cplx* psi, int64_t ldpsi, cplx* T,
                                    double alpha, const double* alpha_dev, const cplx* proj,
