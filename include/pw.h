@@ -370,23 +370,29 @@ pw_status pw_ham_cprj(pw_ham* ham, int64_t nb, void* out_dev, int64_t ldc);
 pw_status pw_upper_bound(pw_ham* ham, double* b_host);
 
 /* ---------------------------------------------------------------------------
- * Launch-shape tuning of H*psi.  A handle starts with the register-resident
- * FFT kernels where they exist, the largest band chunk its buffer holds and
- * 4096 target blocks for the split-K projector product; pw_ham_autotune
- * times alternatives on the device and keeps the fastest.  4096 is the
- * library's own choice: FP64 aims at 512 or 768 blocks for results of few
- * 64 x 64 tiles over short contractions and at 2048 otherwise; FP32 and BF16 split the
- * contraction for 4096, and in the same cases a block may form several of
- * those splits and add them in FP64 (the same sums).  Any other value is taken
- * as it is, by FP64 up to 2048.
+ * Launch-shape tuning of H*psi (pw_ham_plane_kernel says which plane kernel a
+ * choice runs).  A handle starts with the register-resident FFT kernels where
+ * they exist, the largest band chunk its buffer holds and 4096 target blocks
+ * for the split-K projector product; pw_ham_autotune times alternatives on the
+ * device and keeps the fastest.  4096 is the library's own choice: FP64 aims
+ * at 512 or 768 blocks for results of few 64 x 64 tiles over short contractions
+ * and at 2048 otherwise; FP32 and BF16 split the contraction for 4096, and for
+ * few tiles a block may form several of those splits and add them in FP64 (the
+ * same sums).  Any other value is taken as it is, by FP64 up to 2048.
  * ------------------------------------------------------------------------- */
 typedef struct {
   int32_t reg_col;        /* 1: register-resident column kernels (N3 in the fast set)       */
-  int32_t reg_plane;      /* 1: register-resident plane kernel (N1 = N2 in the fast set)     */
-  int32_t plane_variant;  /* FP64 plane kernel: 0 lane groups of up to 16 lanes; 1 up to 8
+  int32_t reg_plane;      /* 1: register-resident plane kernel (N1 = N2 in the fast set);
+                             0: the two-factor kernel where it holds the box (both lengths
+                             in its list and 4 |m| <= N on axes 1 and 2), else the general
+                             one                                                           */
+  int32_t plane_variant;  /* FP64 plane kernel at reg_plane 1: 0 the faster of lane groups of
+                             up to 16 lanes and the two-factor kernel, as measured per
+                             length (two-factor: N1 = N2 = 36, 72); 1 lane groups of up to 8
                              (N1 = N2 = 48, 64, 96)                                        */
-  int32_t plane_variant32;/* FP32 plane kernel: 0, 1 as above (1 also for 120, 128, 144, 160);
-                             2 transforms exchanged through LDS (N1 = N2 = 144)            */
+  int32_t plane_variant32;/* FP32 plane kernel: 0 as above (two-factor: from 36 on except 128
+                             and 160); 1 as above (also for 120, 128, 144, 160); 2 transforms
+                             exchanged through LDS (N1 = N2 = 144)                         */
   int32_t chunk;          /* bands per FFT launch, [1, the handle's buffer]                  */
   int32_t gemm_blocks;    /* split-K target block count of P^H psi, [1, 4096] (FP64: 2049 to
                              4095 act as 2048; 4096 see above)                             */
