@@ -424,6 +424,11 @@ __host__ __device__ inline SplitPlan split_plan(int64_t m, int64_t n, int64_t k,
   p.tiles_m = (m + kBM - 1) / kBM;
   p.tiles_n = (n + kBN - 1) / kBN;
   const int64_t tiles = p.tiles_m * p.tiles_n;
+  if (tiles <= 0) {   // an item without projectors: nothing to form
+    p.nsplit = 1;
+    p.ksplit = k;
+    return p;
+  }
   target = split_target(target, tiles, k);
   int64_t want = (target + tiles - 1) / tiles;
   // at least two K stages per split (short splits keep small products latency-light)
