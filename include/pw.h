@@ -378,7 +378,8 @@ pw_status pw_upper_bound(pw_ham* ham, double* b_host);
  * at 512 or 768 blocks for results of few 64 x 64 tiles over short contractions
  * and at 2048 otherwise; FP32 and BF16 split the contraction for 4096, and for
  * few tiles a block may form several of those splits and add them in FP64 (the
- * same sums).  Any other value is taken as it is, by FP64 up to 2048.
+ * same sums).  Any other value is taken as it is, by FP64 up to 2048; in FP32
+ * and BF16 fewer blocks mean longer FP32 sums.
  * ------------------------------------------------------------------------- */
 typedef struct {
   int32_t reg_col;        /* 1: register-resident column kernels (N3 in the fast set)       */

@@ -1239,10 +1239,8 @@ hipError_t launch_gemm_nn32_s3(int64_t m, int64_t n, int64_t k, double alpha, co
   return hipGetLastError();
 }
 
-int fused_cn32_nsplit(int bf16, int64_t npw, int64_t nb, int64_t nproj, int target) {
-  const SplitPlan p = bf16 ? split_plan32(nproj, nb, npw, target)
-                           : split_plan32(nproj, nb, npw, target);
-  return (int)p.nsplit;
+int fused_cn32_nsplit(int64_t npw, int64_t nb, int64_t nproj, int target) {
+  return (int)split_plan32(nproj, nb, npw, target).nsplit;
 }
 
 hipError_t launch_fused_gemm_cn32(int bf16, int nitems, int64_t m_max, int64_t n_max,

@@ -673,8 +673,8 @@ pw_status fused_setup(pw_batch* b) {
                                                h->gemm_target));
       if (b->prec != PW_FP64)
         g.nsplit_proj32 = std::max(g.nsplit_proj32,
-                                   fused_cn32_nsplit(b->prec == PW_BF16, h->npw, b->items[i].nb,
-                                                     h->nproj, h->gemm_target));
+                                   fused_cn32_nsplit(h->npw, b->items[i].nb, h->nproj,
+                                                     h->gemm_target));
     }
     g.nitems = f.nitems;
     g.nb_max = f.nb_max;

@@ -253,7 +253,7 @@ hipError_t launch_fused_gemm_cn32(int bf16, int nitems, int64_t m_max, int64_t n
                                   int coef_step, hipStream_t s);
 hipError_t launch_fused_gemm_nn32(int bf16, int nitems, int64_t m_max, int64_t n_max,
                                   const ItemDev* D, int sel_c, hipStream_t s);
-int fused_cn32_nsplit(int bf16, int64_t npw, int64_t nb, int64_t nproj, int target);
+int fused_cn32_nsplit(int64_t npw, int64_t nb, int64_t nproj, int target);
 
 // Fused-batch subspace and filter steps (one launch over all items):
 //   FS_CHEB_COEF (arg0 = degree), FS_FILTER_FIRST (arg0 = 1: FP32 b32[1], 0: FP64 blk),
