@@ -1022,9 +1022,10 @@ __host__ __device__ inline SplitPlan split_plan32(int64_t m, int64_t n, int64_t 
 //   bf16  36065 x 4, 8, 16, 32      39 33, 75 43, 95 61, 127 91   67773 x 16, 24        121 92, 148 152
 //         135421 x 8, 15, 20        137 104, 173 161, 198 209
 // (more than 32 tiles: 131 194 for 40 over 36065).  FP32 sums over all a workgroup
-// reads would save some more (36065 x 8: 71 and 35), but their errors are up to 2.4
-// times as large (37073 values, 12 tiles: 1.0e-7 instead of 4.2e-8).  Two splits at
-// a time leave too few workgroups (bf16 17168 x 3: 12.4 instead of 10.2).
+// reads would save some more (36065 x 8: 71 and 35), but the projections' error
+// against 64 bits grows: 256 x 160 over 37073 values 2.5e-7 -> 3.7e-7, random values
+// 2.6e-7 -> 7.1e-7; 192 x 117 over 16346 2.1e-7 -> 2.5e-7.  Two splits at a time leave
+// too few workgroups (bf16 17168 x 3: 12.4 instead of 10.2).
 constexpr int kWideTarget = 512;
 struct WidePlan {
   SplitPlan p;
